@@ -12,6 +12,7 @@
 // the same expressions.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stdint.h>
 
 namespace tpcca {
 
@@ -52,6 +53,58 @@ __host__ __device__ __forceinline__ float sqrt_rn_normal(float x) {
 #endif
 }
 
+// Correctly rounded quotients and roots without the library sequences'
+// scaling for extreme exponents (about ten instructions each, in every step
+// of the dependent chain that bounds the fits).  1 / x: the hardware
+// reciprocal (one ulp) and one fused Newton step give the correctly rounded
+// quotient for every float with 2^-125 <= |x| <= 2^125, and NaN for NaN;
+// sqrt(x): g = x rsq(x) and one fused correction give the correctly rounded
+// root for every float in [2^-96, 2^97] (both checked against the library's
+// results over all bit patterns of these ranges).  The host build takes the
+// library operations, which round the same.
+__host__ __device__ __forceinline__ float rcp_rn(float x) {   // 2^-125 <= |x| <= 2^125, or NaN
+#if defined(__HIP_DEVICE_COMPILE__)
+  const float y = __builtin_amdgcn_rcpf(x);
+  return fmaf(fmaf(-x, y, 1.0f), y, y);
+#else
+  return 1.0f / x;
+#endif
+}
+__host__ __device__ __forceinline__ float rcp_rn_special(float x) {   // as rcp_rn, and x = 0 or infinite
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_div_fixupf(rcp_rn(x), x, 1.0f);
+#else
+  return 1.0f / x;
+#endif
+}
+__host__ __device__ __forceinline__ float sqrt_rn_pos(float x) {   // 2^-96 <= x <= 2^97
+#if defined(__HIP_DEVICE_COMPILE__)
+  const float y = __builtin_amdgcn_rsqf(x);
+  const float g = x * y;
+  return fmaf(fmaf(-g, g, x), 0.5f * y, g);
+#else
+  return sqrtf(x);
+#endif
+}
+__host__ __device__ __forceinline__ uint32_t f32_bits(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __float_as_uint(x);
+#else
+  union { float f; uint32_t u; } v{x};
+  return v.u;
+#endif
+}
+// |x| in [2^-125, 2^125], as a bound on a key that two values can share:
+// rcp_key(x) <= kRcpKey (one shift-add; the larger of two keys tests both).
+constexpr uint32_t kRcpKey = 250u << 24;
+__host__ __device__ __forceinline__ uint32_t rcp_key(float x) { return (f32_bits(x) << 1) - (2u << 24); }
+// 1 / x for any x
+__host__ __device__ __forceinline__ float rcp_rn_any(float x) {
+  float r = rcp_rn(x);
+  if (__builtin_expect(rcp_key(x) > kRcpKey, 0)) r = 1.0f / x;
+  return r;
+}
+
 // One step of the helix from the plane x0 to the plane x1.  The sine of the
 // direction moves linearly (s1 = s0 + kap dx); the chord rises by
 // dx (s0 + s1)/(c0 + c1); the transverse path is the chord (signed like dx)
@@ -71,27 +124,30 @@ __host__ __device__ __forceinline__ bool transport(float p[5], float C[15], floa
   const float s1 = fmaf(kap, dx, s0);
   if (!(fabsf(s1) < m.sin_max)) return false;
   const float c0 = sqrt_rn_normal(fmaf(-s0, s0, 1.0f));
-  const float c1 = sqrt_rn_normal(fmaf(-s1, s1, 1.0f));
+  const float c1 = sqrt_rn_pos(fmaf(-s1, s1, 1.0f));   // (|s1| < sin_max < 1: at least 2^-24)
   const float ss = s0 + s1;
   const float cc = c0 + c1;
-  const float icc = 1.0f / cc;   // shared denominator: one division, then products
+  const float icc = rcp_rn(cc);   // shared denominator: one division, then products (cc >= 2^-12 or NaN)
   const float tn = ss * icc;
   const float dy = dx * tn;
-  float d = sqrtf(fmaf(dx, dx, dy * dy));
-  if (dx < 0.0f) d = -d;
+  const float dd = fmaf(dx, dx, dy * dy);
+  float d = sqrt_rn_pos(dd);
+  float id = rcp_rn(d);
+  // (steps of less than 2^-45 or more than 2^45 cm, or a NaN: never in a detector)
+  if (__builtin_expect(f32_bits(dd) - (37u << 23) > (180u << 23), 0)) { d = sqrtf(dd); id = 1.0f / d; }
+  if (dx < 0.0f) { d = -d; id = -id; }
   const float u = (kap * d) * 0.5f;
   const float u2 = u * u;
   const float g = fmaf(u2, fmaf(u2, fmaf(u2, fmaf(u2, A4, A3), A2), A1), 1.0f);
   const float gp = u * fmaf(u2, fmaf(u2, fmaf(u2, B4, B3), B2), B1);
   const float l = d * g;
-  const float i01 = 1.0f / (c0 * c1);   // the two tangents share one division
+  const float i01 = rcp_rn_special(c0 * c1);   // the two tangents share one division (c0 may be 0)
   const float t0 = (s0 * c1) * i01;
   const float t1 = (s1 * c0) * i01;
   const float dtn_ds = fmaf(tn, t0 + t1, 2.0f) * icc;
   const float dtn_dk = (f * fmaf(tn, t1, 1.0f)) * icc;
   const float a = dx * dtn_ds;
   const float b = dx * dtn_dk;
-  const float id = 1.0f / d;
   const float dd_ds = (dy * a) * id;
   const float dd_dk = (dy * b) * id;
   const float du_ds = (kap * dd_ds) * 0.5f;
@@ -146,7 +202,7 @@ __host__ __device__ __forceinline__ void update(float p[5], float C[15], float m
   const float S01 = C[1];
   const float S11 = C[5] + m.vz;
   const float det = fmaf(S00, S11, -(S01 * S01));
-  const float idet = 1.0f / det;
+  const float idet = rcp_rn_any(det);
   const float I00 = S11 * idet;
   const float I01 = (-S01) * idet;
   const float I11 = S00 * idet;
