@@ -22,6 +22,10 @@ __host__ __device__ inline uint32_t grid_cells(uint32_t n) {
   return c < (uint32_t)kMaxCells ? c : (uint32_t)kMaxCells;
 }
 
+// Entries past the end of the grid-ordered array that a search may load
+// (and never uses).
+constexpr int kGridPad = 8;
+
 // Flags / counters in device memory.
 enum : int {
   F_ERR = 0,        // error bits (below)
@@ -40,19 +44,18 @@ enum : uint32_t { ERR_INVALID = 1u, ERR_LIMIT = 2u, ERR_STUCK = 4u };
 
 // Per-(event, sector, row) search grid: cells of a uniform 2-D (z, y) grid
 // over the row's bounding box; cell (iz, iy) = cell_base + iz * ny + iy.
+// 32 bytes, two 16-byte loads per search step.
 struct alignas(16) GridParams {
   uint32_t cell_base;
-  uint32_t nz, ny;
+  uint32_t base;        // the row unit's first entry in the grid-ordered array
+  uint32_t dims;        // nz | ny << 13 (at most kMaxCells = 4097 each)
+  uint32_t pad;
   float z0, y0, inv_bz, inv_by;
-  uint32_t base;        // the row unit's first entry in the grid-ordered arrays
-  uint32_t off_plane;   // 1: some cluster of the row unit has x other than the row's plane
+  __host__ __device__ uint32_t nz() const { return dims & 0x1FFFu; }
+  __host__ __device__ uint32_t ny() const { return dims >> 13; }
+  static __host__ __device__ uint32_t pack(uint32_t nz, uint32_t ny) { return nz | (ny << 13); }
 };
-
-// Grid-ordered record of the tracklet search: (y, z, canonical position).
-struct SearchRec {
-  float y, z;
-  uint32_t pos;
-};
+static_assert(kMaxCells < (1 << 13), "grid dimensions in 13 bits");
 
 struct EventIn {
   const float* x;
@@ -135,8 +138,7 @@ struct Ws {
   uint32_t* cid;        // event-local cluster id
   uint32_t* cru;        // row unit
   // grid-ordered copy for window searches: (y, z, x, canonical position)
-  float4* gbuf;         // [N]
-  SearchRec* grec;      // [N] the same entries without x (the tracklet search's records)
+  float4* gbuf;         // [N + kGridPad] (the tracklet search may load past a row unit's end)
   uint16_t* cell_off;   // [kCellsPerCluster N + 2 RU + 1] (grid_cells + 1 per row unit), relative to the
                         // row unit's first entry (rows hold at most TPCCA_MAX_ROW_CLUSTERS < 2^16)
   // links (canonical positions)

@@ -16,6 +16,7 @@
 //   a7 final fit  outermost-to-innermost Kalman refit of the owned hits,
 //                 ordered compaction into the caller's flat buffers
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.hpp"
 #include "kf_c2.hpp"
@@ -463,7 +464,7 @@ __device__ __forceinline__ uint32_t cell_coord(float v, float v0, float inv, uin
 }
 
 __device__ __forceinline__ uint32_t cell_of(const GridParams& G, float y, float z) {
-  return cell_coord(z, G.z0, G.inv_bz, G.nz) * G.ny + cell_coord(y, G.y0, G.inv_by, G.ny);
+  return cell_coord(z, G.z0, G.inv_bz, G.nz()) * G.ny() + cell_coord(y, G.y0, G.inv_by, G.ny());
 }
 
 // Search grid of a row unit of n clusters with the given bounding box: about
@@ -481,11 +482,10 @@ __device__ __forceinline__ GridParams make_grid(uint32_t n, uint32_t cbase, uint
     ny = (uint32_t)fminf(fmaxf(dy / a, 1.0f), (float)(cap / nz));
   }
   GridParams G;
-  G.cell_base = cbase; G.nz = nz; G.ny = ny; G.z0 = zmin; G.y0 = ymin;
+  G.cell_base = cbase; G.base = off; G.dims = GridParams::pack(nz, ny); G.pad = 0u;
+  G.z0 = zmin; G.y0 = ymin;
   G.inv_bz = dz > 0.0f ? (float)nz / dz : 0.0f;
   G.inv_by = dy > 0.0f ? (float)ny / dy : 0.0f;
-  G.base = off;
-  G.off_plane = 0u;
   return G;
 }
 
@@ -548,10 +548,9 @@ __global__ __launch_bounds__(TB) void k_rows_tiny(Ws w) {
     zmin = fminf(zmin, __shfl_xor(zmin, d, 64)); zmax = fmaxf(zmax, __shfl_xor(zmax, d, 64));
   }
   // grid parameters: every lane computes the same values, lane 0 stores them
-  GridParams G = make_grid(n, cbase, off, ymin, ymax, zmin, zmax);
-  G.off_plane = __ballot(mine && x != w.row_x[ru % w.R]) ? 1u : 0u;
+  const GridParams G = make_grid(n, cbase, off, ymin, ymax, zmin, zmax);
   if (lane == 0) w.grid[ru] = G;
-  const uint32_t nc = G.nz * G.ny;
+  const uint32_t nc = G.nz() * G.ny();
   for (uint32_t c = lane; c <= nc; c += 64) hist[c] = 0u;
   wave_sync();
   const uint32_t cell = mine ? cell_of(G, y, z) : 0u;
@@ -570,7 +569,6 @@ __global__ __launch_bounds__(TB) void k_rows_tiny(Ws w) {
   if (mine) {
     const uint32_t pos = atomicAdd(&hist[cell], 1u);
     w.gbuf[off + pos] = make_float4(y, z, x, __uint_as_float(off + lane));
-    w.grec[off + pos] = SearchRec{y, z, off + lane};
   }
 }
 
@@ -630,8 +628,6 @@ __global__ __launch_bounds__(TB) void k_rows_wave(Ws w) {
     }
     float px[4], py[4], pz[4];
     float ymin = INFINITY, ymax = -INFINITY, zmin = INFINITY, zmax = -INFINITY;
-    const float xr = w.row_x[ru % w.R];
-    bool offp = false;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const uint32_t i = 4u * lane + k;
@@ -642,7 +638,6 @@ __global__ __launch_bounds__(TB) void k_rows_wave(Ws w) {
         w.cx[off + i] = v.x; w.cy[off + i] = v.y; w.cz[off + i] = v.z;
         w.cid[off + i] = K[k]; w.cru[off + i] = (uint32_t)ru;
         ymin = fminf(ymin, v.y); ymax = fmaxf(ymax, v.y); zmin = fminf(zmin, v.z); zmax = fmaxf(zmax, v.z);
-        offp = offp || v.x != xr;
       }
     }
 #pragma unroll
@@ -651,10 +646,9 @@ __global__ __launch_bounds__(TB) void k_rows_wave(Ws w) {
       zmin = fminf(zmin, __shfl_xor(zmin, d, 64)); zmax = fmaxf(zmax, __shfl_xor(zmax, d, 64));
     }
     // every lane computes the same grid, lane 0 stores it
-    GridParams G = make_grid(n, cbase, off, ymin, ymax, zmin, zmax);
-    G.off_plane = __ballot(offp) ? 1u : 0u;
+    const GridParams G = make_grid(n, cbase, off, ymin, ymax, zmin, zmax);
     if (lane == 0) w.grid[ru] = G;
-    const uint32_t nc = G.nz * G.ny;
+    const uint32_t nc = G.nz() * G.ny();
     for (uint32_t c = lane; c <= nc; c += 64) hist[c] = 0u;
     wave_sync();
     uint32_t cell[4];
@@ -680,7 +674,6 @@ __global__ __launch_bounds__(TB) void k_rows_wave(Ws w) {
       if (i < n) {
         const uint32_t pos = atomicAdd(&hist[cell[k]], 1u);
         w.gbuf[off + pos] = make_float4(py[k], pz[k], px[k], __uint_as_float(off + i));
-        w.grec[off + pos] = SearchRec{py[k], pz[k], off + i};
       }
     }
   };
@@ -708,7 +701,6 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
   // slots (16 bit) during the sort, then the cell histogram
   __shared__ uint32_t s_aux[(kCells + 1) > kIds / 2 ? (kCells + 1) : kIds / 2];
   __shared__ float s_red[4][TB / 64];
-  __shared__ uint32_t s_off[TB / 64];
   __shared__ GridParams s_gp;
   uint16_t* s_slot = (uint16_t*)s_aux;
   uint32_t* s_hist = s_aux;
@@ -722,7 +714,7 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
     if (n > (uint32_t)kMaxRow) {
       if (tid == 0) {
         atomicOr(&w.flags[F_ERR], ERR_LIMIT);
-        GridParams G{cbase, 1u, 1u, 0.f, 0.f, 0.f, 0.f, off, 1u};
+        GridParams G{cbase, off, GridParams::pack(1u, 1u), 0u, 0.f, 0.f, 0.f, 0.f};
         w.grid[ru] = G;
         w.cell_off[cbase] = 0;
         w.cell_off[cbase + 1] = 0;
@@ -735,7 +727,6 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
         w.cx[off + k] = nan; w.cy[off + k] = nan; w.cz[off + k] = nan;
         w.cid[off + k] = 0u; w.cru[off + k] = (uint32_t)ru;
         w.gbuf[off + k] = make_float4(nan, nan, nan, __uint_as_float(off + k));
-        w.grec[off + k] = SearchRec{nan, nan, off + k};
       }
       return;
     }
@@ -749,8 +740,6 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
     uint32_t K[4], V[4];
     float px[4], py[4], pz[4];
     float ymin = INFINITY, ymax = -INFINITY, zmin = INFINITY, zmax = -INFINITY;
-    const float xr = w.row_x[ru % w.R];
-    bool offp = false;
     if (fast) {
   #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -810,7 +799,6 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
           w.cx[off + i] = v.x; w.cy[off + i] = v.y; w.cz[off + i] = v.z;
           w.cid[off + i] = K[k]; w.cru[off + i] = (uint32_t)ru;
           ymin = fminf(ymin, v.y); ymax = fmaxf(ymax, v.y); zmin = fminf(zmin, v.z); zmax = fmaxf(zmax, v.z);
-          offp = offp || v.x != xr;
         }
       }
     } else {
@@ -843,7 +831,6 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
         w.cx[off + k] = x; w.cy[off + k] = y; w.cz[off + k] = z;
         w.cid[off + k] = s_ids[k]; w.cru[off + k] = (uint32_t)ru;
         ymin = fminf(ymin, y); ymax = fmaxf(ymax, y); zmin = fminf(zmin, z); zmax = fmaxf(zmax, z);
-        offp = offp || x != xr;
       }
     }
   #pragma unroll
@@ -851,27 +838,22 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
       ymin = fminf(ymin, __shfl_xor(ymin, d, 64)); ymax = fmaxf(ymax, __shfl_xor(ymax, d, 64));
       zmin = fminf(zmin, __shfl_xor(zmin, d, 64)); zmax = fmaxf(zmax, __shfl_xor(zmax, d, 64));
     }
-    const bool offw = __ballot(offp) != 0ull;
     if (lane_id() == 0) {
       s_red[0][tid >> 6] = ymin; s_red[1][tid >> 6] = ymax; s_red[2][tid >> 6] = zmin; s_red[3][tid >> 6] = zmax;
-      s_off[tid >> 6] = offw ? 1u : 0u;
     }
     __syncthreads();
     if (tid == 0) {
-      uint32_t o = s_off[0];
       for (int i = 1; i < TB / 64; ++i) {
         ymin = fminf(ymin, s_red[0][i]); ymax = fmaxf(ymax, s_red[1][i]);
         zmin = fminf(zmin, s_red[2][i]); zmax = fmaxf(zmax, s_red[3][i]);
-        o |= s_off[i];
       }
-      GridParams G = make_grid(n, cbase, off, ymin, ymax, zmin, zmax);
-      G.off_plane = o;
+      const GridParams G = make_grid(n, cbase, off, ymin, ymax, zmin, zmax);
       s_gp = G;
       w.grid[ru] = G;
     }
     __syncthreads();
     const GridParams G = s_gp;
-    const uint32_t nc = G.nz * G.ny;
+    const uint32_t nc = G.nz() * G.ny();
     for (uint32_t c = tid; c <= nc; c += TB) s_hist[c] = 0u;
     __syncthreads();
     if (fast) {
@@ -902,7 +884,6 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
         if (i < n) {
           const uint32_t slot = atomicAdd(&s_hist[cell_of(G, py[k], pz[k])], 1u);
           w.gbuf[off + slot] = make_float4(py[k], pz[k], px[k], __uint_as_float(off + i));
-          w.grec[off + slot] = SearchRec{py[k], pz[k], off + i};
         }
       }
     } else {
@@ -910,7 +891,6 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
         const float x = w.cx[off + k], y = w.cy[off + k], z = w.cz[off + k];
         const uint32_t slot = atomicAdd(&s_hist[cell_of(G, y, z)], 1u);
         w.gbuf[off + slot] = make_float4(y, z, x, __uint_as_float(off + k));
-        w.grec[off + slot] = SearchRec{y, z, off + k};
       }
     }
   };
@@ -932,10 +912,10 @@ struct CellBox { uint32_t iz0, iz1, iy0, iy1; };
 __device__ __forceinline__ CellBox cell_box(const GridParams& G, float yq, float zq, float wy, float wz) {
   const float m = 1e-3f;
   CellBox b;
-  b.iz0 = cell_coord(zq - wz - m, G.z0, G.inv_bz, G.nz);
-  b.iz1 = cell_coord(zq + wz + m, G.z0, G.inv_bz, G.nz);
-  b.iy0 = cell_coord(yq - wy - m, G.y0, G.inv_by, G.ny);
-  b.iy1 = cell_coord(yq + wy + m, G.y0, G.inv_by, G.ny);
+  b.iz0 = cell_coord(zq - wz - m, G.z0, G.inv_bz, G.nz());
+  b.iz1 = cell_coord(zq + wz + m, G.z0, G.inv_bz, G.nz());
+  b.iy0 = cell_coord(yq - wy - m, G.y0, G.inv_by, G.ny());
+  b.iy1 = cell_coord(yq + wy + m, G.y0, G.inv_by, G.ny());
   return b;
 }
 
@@ -958,14 +938,14 @@ __device__ __forceinline__ void find_pair(const Ws& w, float xi, float yi, float
   float bs = 0.0f;
   bu = -1; bd = -1;
   for (uint32_t izd = bdn.iz0; izd <= bdn.iz1; ++izd) {
-    const uint32_t cd0 = izd * Gd.ny;
+    const uint32_t cd0 = izd * Gd.ny();
     const uint32_t kd1 = Dc[cd0 + bdn.iy1 + 1];
     for (uint32_t kd = Dc[cd0 + bdn.iy0]; kd < kd1; ++kd) {
       const float4 D = D4[kd];
       if (!(fabsf(D.x - yi) <= WY && fabsf(D.y - zi) <= WZ)) continue;
       const int32_t pd = (int32_t)__float_as_uint(D.w);
       for (uint32_t izu = bup.iz0; izu <= bup.iz1; ++izu) {
-        const uint32_t cu0 = izu * Gu.ny;
+        const uint32_t cu0 = izu * Gu.ny();
         const uint32_t ku1 = Uc[cu0 + bup.iy1 + 1];
         for (uint32_t ku = Uc[cu0 + bup.iy0]; ku < ku1; ++ku) {
           const float4 U = U4[ku];
@@ -994,7 +974,7 @@ __device__ __forceinline__ int collect(const GridParams& G, F4 D4, U32 Dc, float
   const CellBox b = cell_box(G, yi, zi, WY, WZ);
   int n = 0;
   for (uint32_t iz = b.iz0; iz <= b.iz1; ++iz) {
-    const uint32_t c0 = iz * G.ny;
+    const uint32_t c0 = iz * G.ny();
     const uint32_t k0 = Dc[c0 + b.iy0], k1 = Dc[c0 + b.iy1 + 1];
     // four entries read before any is tested
     for (uint32_t k = k0; k < k1; k += 4) {
@@ -1231,7 +1211,7 @@ __global__ __launch_bounds__(TB) void k_links(Ws w) {
       // neither the loads nor the stores need a branch
       constexpr int kE = (int)((kS + kG - 1) / kG);                          // entries per thread
       constexpr int kC = (int)((kCellsPerCluster * kS + 1 + kG) / kG);      // cell offsets per thread
-      const uint32_t ncd = Gd.nz * Gd.ny, ncu = Gu.nz * Gu.ny;
+      const uint32_t ncd = Gd.nz() * Gd.ny(), ncu = Gu.nz() * Gu.ny();
   #pragma unroll
       for (int j = 0; j < kE; ++j) {
         const uint32_t i = gt + kG * (uint32_t)j;
@@ -1434,71 +1414,134 @@ __global__ __launch_bounds__(TB) void k_start_tap(Ws w) {
 }
 
 // ----------------------------------------------------------- a5: tracklets
-struct Found { int32_t pos; float y, z; };
+struct Found { int32_t pos; float y, z, x; };
 
-// Closest cluster of row unit ru to the predicted (y, z):
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xF, 0xF, true);
+}
+template <int kCtrl>
+__device__ __forceinline__ float dpp_f32(float v) { return __uint_as_float(dpp_u32<kCtrl>(__float_as_uint(v))); }
+// Lane exchanges inside groups of two, four and eight lanes (the last one
+// mirrors the eight: enough once each four hold one value).
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppMirror8 = 0x141;
+
+template <int G, class F>
+__device__ __forceinline__ void group_steps(F&& f) {
+  if constexpr (G >= 2) f(std::integral_constant<int, kDppXor1>{});
+  if constexpr (G >= 4) f(std::integral_constant<int, kDppXor2>{});
+  if constexpr (G >= 8) f(std::integral_constant<int, kDppMirror8>{});
+}
+
+// Closest cluster of a row unit (grid Q) to the predicted (y, z):
 // d = dy^2/(Cyy + sy^2) + dz^2/(Czz + sz^2) <= chi2_ext, minimum (d, id).
-// The candidates are the 12-byte (y, z, canonical position) search records
-// (the winner's x is read from the canonical arrays only in row units with
-// clusters off the row plane).  The cell ranges of the box's first two z
-// rows are read together, then their entries in chunks of eight loads issued
-// before any is tested, so a step waits for memory twice rather than once
-// per candidate.  The result does not depend on the order the candidates
-// are visited in.
-__device__ __forceinline__ Found search_row(const Ws& w, const GridParams& G, const float p[5],
-                                            const float C[15]) {
+// The box's first two z rows are two ranges of the grid-ordered array whose
+// bounds are read together; then their entries, the first ones of both
+// ranges issued before any is tested, so a step waits for memory twice
+// rather than once per candidate.  With one lane per seed (G = 1) a lane
+// loads two entries of each range at once and two more where a range holds
+// them; with a group of G lanes per seed half of the lanes take the entries
+// of each range, and the group's minimum is the result.  Loads may pass the
+// range's end (kGridPad entries beyond the array): those entries are masked.
+// The result does not depend on the order the candidates are visited in.
+template <int G>
+__device__ __forceinline__ Found search_row(const Ws& w, const GridParams& Q, const float p[5],
+                                            const float C[15], int gl) {
   const float sy2 = C[0] + w.m.vy, sz2 = C[5] + w.m.vz;
-  const float isy = 1.0f / sy2, isz = 1.0f / sz2;
-  const float CUT = w.P.chi2_ext;
+  float isy = rcp_rn(sy2), isz = rcp_rn(sz2);
+  if (__builtin_expect(max(rcp_key(sy2), rcp_key(sz2)) > kRcpKey, 0)) { isy = 1.0f / sy2; isz = 1.0f / sz2; }
   // the window only bounds the cells scanned: the hardware square root
-  // (1 ulp) is enough under the 1e-4 relative and 1e-3 cm margins, which
-  // keep the scanned cells a superset of every cluster passing the cut
-  const float wy = 3.0f * __builtin_amdgcn_sqrtf(sy2) * 1.0001f;
-  const float wz = 3.0f * __builtin_amdgcn_sqrtf(sz2) * 1.0001f;
-  const CellBox b = cell_box(G, p[0], p[1], wy, wz);
+  // (1 ulp) is enough under the 1e-4 relative and 1e-3 cm margins; the
+  // bounds are taken in cells, with 2e-3 cells for the rounding there
+  // (coordinates of at most 4097 cells), so the scanned cells stay a
+  // superset of those of every cluster passing the cut
+  const float wy = 3.0003f * __builtin_amdgcn_sqrtf(sy2) + 1e-3f;
+  const float wz = 3.0003f * __builtin_amdgcn_sqrtf(sz2) + 1e-3f;
+  const uint32_t nz = Q.nz(), ny = Q.ny();
+  const float fz = (float)(nz - 1u), fy = (float)(ny - 1u);
+  const float tz = (p[1] - Q.z0) * Q.inv_bz, hz = fmaf(wz, Q.inv_bz, 2e-3f);
+  const float ty = (p[0] - Q.y0) * Q.inv_by, hy = fmaf(wy, Q.inv_by, 2e-3f);
+  // (a NaN bound takes cell 0)
+  const uint32_t iz0 = (uint32_t)fminf(fmaxf(tz - hz, 0.0f), fz), iz1 = (uint32_t)fminf(fmaxf(tz + hz, 0.0f), fz);
+  const uint32_t iy0 = (uint32_t)fminf(fmaxf(ty - hy, 0.0f), fy), iy1 = (uint32_t)fminf(fmaxf(ty + hy, 0.0f), fy) + 1u;
   // (bd, pos) starts at (CUT, INT32_MAX): the first candidate with d <= CUT
   // replaces it, later ones must beat the best so far, so no separate test
   // of the cut (a NaN distance fails every comparison)
-  Found best{INT32_MAX, 0.f, 0.f};
-  float bd = CUT;
-  auto consider = [&](const SearchRec& c) {
-    const float dY = c.y - p[0], dZ = c.z - p[1];
+  Found best{INT32_MAX, 0.f, 0.f, 0.f};
+  float bd = w.P.chi2_ext;
+  auto consider = [&](const float4& c, bool in) {
+    const float dY = c.x - p[0], dZ = c.y - p[1];
     const float d = fmaf(dZ * dZ, isz, (dY * dY) * isy);
-    const int32_t pos = (int32_t)c.pos;
-    if (d < bd || (d == bd && pos < best.pos)) { best = Found{pos, c.y, c.z}; bd = d; }
+    const int32_t pos = (int32_t)__float_as_uint(c.w);
+    const bool take = in & ((d < bd) | ((d == bd) & (pos < best.pos)));
+    best.pos = take ? pos : best.pos;
+    best.y = take ? c.x : best.y;
+    best.z = take ? c.y : best.z;
+    best.x = take ? c.z : best.x;
+    bd = take ? d : bd;
   };
-  const uint32_t nzr = b.iz1 - b.iz0 + 1;
-  const uint32_t c0a = G.cell_base + b.iz0 * G.ny;
-  const uint32_t c0b = c0a + G.ny;
-  const uint32_t ka0 = G.base + w.cell_off[c0a + b.iy0], ka1 = G.base + w.cell_off[c0a + b.iy1 + 1];
-  uint32_t kb0 = 0, kb1 = 0;
-  if (nzr > 1) { kb0 = G.base + w.cell_off[c0b + b.iy0]; kb1 = G.base + w.cell_off[c0b + b.iy1 + 1]; }
-  // entries of the two ranges as one sequence t = 0 .. na + nb - 1
-  const uint32_t na = ka1 - ka0, nt = na + (kb1 - kb0);
-  constexpr uint32_t kChunk = 8;
-  for (uint32_t t0 = 0; t0 < nt; t0 += kChunk) {
-    SearchRec c[kChunk];
-#pragma unroll
-    for (uint32_t j = 0; j < kChunk; ++j) {
-      const uint32_t t = t0 + j;
-      if (t < nt) c[j] = w.grec[t < na ? ka0 + t : kb0 + (t - na)];
+  const uint32_t nzr = iz1 - iz0 + 1u;
+  const uint16_t* ca = w.cell_off + (Q.cell_base + iz0 * ny);
+  const uint16_t* cb = ca + (nzr > 1u ? ny : 0u);
+  const float4* g = w.gbuf + Q.base;
+  const uint32_t a0 = ca[iy0], a1 = ca[iy1], b0 = cb[iy0], b1 = cb[iy1];
+  const uint32_t na = a1 - a0, nb = nzr > 1u ? b1 - b0 : 0u;
+  if constexpr (G == 1) {
+    const float4* ga = g + a0;
+    const float4* gb = g + b0;
+    const float4 A0 = ga[0], A1 = ga[1], B0 = gb[0], B1 = gb[1];
+    if (max(na, nb) > 2u) {
+      const float4 A2 = ga[2], A3 = ga[3], B2 = gb[2], B3 = gb[3];
+      consider(A2, na > 2u); consider(A3, na > 3u);
+      consider(B2, nb > 2u); consider(B3, nb > 3u);
+      for (uint32_t k = 4; k < na; ++k) consider(ga[k], true);
+      for (uint32_t k = 4; k < nb; ++k) consider(gb[k], true);
     }
-#pragma unroll
-    for (uint32_t j = 0; j < kChunk; ++j)
-      if (t0 + j < nt) consider(c[j]);
-  }
-  for (uint32_t iz = 2; iz < nzr; ++iz) {
-    const uint32_t cz = G.cell_base + (b.iz0 + iz) * G.ny;
-    const uint32_t k0 = G.base + w.cell_off[cz + b.iy0], k1 = G.base + w.cell_off[cz + b.iy1 + 1];
-    for (uint32_t k = k0; k < k1; k += 4) {
-      SearchRec c[4];
-#pragma unroll
-      for (uint32_t j = 0; j < 4; ++j)
-        if (k + j < k1) c[j] = w.grec[k + j];
-#pragma unroll
-      for (uint32_t j = 0; j < 4; ++j)
-        if (k + j < k1) consider(c[j]);
+    consider(A0, na > 0u); consider(A1, na > 1u);
+    consider(B0, nb > 0u); consider(B1, nb > 1u);
+    for (uint32_t iz = 2; iz < nzr; ++iz) {
+      const uint16_t* cz = ca + iz * ny;
+      const uint32_t k0 = cz[iy0], k1 = cz[iy1];
+      for (uint32_t k = k0; k < k1; ++k) consider(g[k], true);
     }
+  } else {
+    constexpr uint32_t H = G / 2;
+    const bool side = gl >= (int)H;
+    const uint32_t n = side ? nb : na, j = (uint32_t)gl & (H - 1u);
+    const float4* gs = g + ((side ? b0 : a0) + j);
+    const float4 c0 = gs[0];
+    if (n > j + H) {
+      const float4 c1 = gs[H];
+      consider(c1, true);
+      for (uint32_t k = j + 2u * H; k < n; k += H) consider(g[(side ? b0 : a0) + k], true);
+    }
+    consider(c0, j < n);
+    for (uint32_t iz = 2; iz < nzr; ++iz) {
+      const uint16_t* cz = ca + iz * ny;
+      const uint32_t k0 = cz[iy0], k1 = cz[iy1];
+      for (uint32_t k = k0 + (uint32_t)gl; k < k1; k += G) consider(g[k], true);
+    }
+    // the group's minimum (d, pos), then the winner's coordinates (one lane
+    // of the group holds it: or over the group)
+    const int32_t mine = best.pos;
+    group_steps<G>([&](auto ctl) {
+      const float od = dpp_f32<ctl.value>(bd);
+      const int32_t op = (int32_t)dpp_u32<ctl.value>((uint32_t)best.pos);
+      const bool take = (od < bd) | ((od == bd) & (op < best.pos));
+      bd = take ? od : bd;
+      best.pos = take ? op : best.pos;
+    });
+    const bool won = mine == best.pos;
+    uint32_t uy = won ? __float_as_uint(best.y) : 0u, uz = won ? __float_as_uint(best.z) : 0u;
+    uint32_t ux = won ? __float_as_uint(best.x) : 0u;
+    group_steps<G>([&](auto ctl) {
+      uy |= dpp_u32<ctl.value>(uy);
+      uz |= dpp_u32<ctl.value>(uz);
+      ux |= dpp_u32<ctl.value>(ux);
+    });
+    best.y = __uint_as_float(uy);
+    best.z = __uint_as_float(uz);
+    best.x = __uint_as_float(ux);
   }
   if (best.pos == INT32_MAX) best.pos = -1;
   return best;
@@ -1519,44 +1562,59 @@ __device__ __forceinline__ bool accepted(float X, const Acc& a, const float p[5]
 //   BACK   transport back to the seed's first row, at most kBackRows rows
 //          per step, no updates;
 //   DOWN   as UP, downward from the row below the seed.
-// A lane that finishes writes its tracklet and takes the next seed from a
-// device counter (one atomic per wave).  The seed list is split into kXcd
-// contiguous ranges with a counter each; a workgroup starts on the range of
-// its XCD and moves on to the others once that one is used up.
+// Bound by the dependent chain of a seed: about 162 steps, each the scalar
+// chain of a transport, two memory round trips of the search (cell offsets,
+// entries) and an update.  What is not on that chain is kept short: the next
+// step's plane, grid and chain record are loaded before the update, which
+// covers their latency; phase changes are settled in one place; quotients
+// and roots take the short sequences.  On one sector's 17 k clusters the
+// kernel takes 277 us (476 with one lane per seed, a test per loaded entry
+// and no L2 warming), on 0.77 M clusters 345 (494), on 3.8 M, where three
+// waves per SIMD share the issue slots, 770 (805).
+// Lanes that have finished wait until a quarter of the wave does (or the
+// whole wave has): then they write their tracklets and take the next seeds
+// from a device counter (one atomic per wave).  The seed list is split into
+// kXcd contiguous ranges with a counter each; a workgroup starts on the
+// range of its XCD and moves on to the others once that one is used up.
 enum : int { ST_CHAIN = 0, ST_UP = 1, ST_BACK = 2, ST_DOWN = 3, ST_DONE = 4, ST_IDLE = 5 };
 
-__global__ __launch_bounds__(TB) void k_tracklets(Ws w) {
-  __shared__ float sX[256];
-  for (int r = threadIdx.x; r < w.R; r += TB) sX[r] = w.row_x[r];
-  __syncthreads();
+// G lanes per seed: every lane of a group holds the same state (the same
+// expressions of the same values), the row search is shared out.
+template <int G>
+__device__ __forceinline__ void tracklets_wave(const Ws& w, const float* sX, const uint32_t ns) {
   const Acc acc{w.tan_a, w.z_max};
-  const uint32_t ns = w.flags[F_NSEEDS];
-  // when the lanes of the lower workgroups already outnumber the seeds they
-  // take (and, by refills, finish) them all: this one has nothing to do
-  if ((int64_t)blockIdx.x * TB >= (int64_t)ns) return;
   const int R = w.R;
+  const int gl = lane_id() & (G - 1);
+  const uint64_t groups_before = (1ull << (lane_id() & ~(G - 1))) - 1ull;
   int phase = ST_IDLE;
-  int64_t s = -1;
-  int32_t* hits = nullptr;
+  bool more = true;   // (wave-uniform) seeds may be left
+  uint32_t s = 0;
   int32_t h0 = 0, nxt = -1;
   int r0 = 0, r = 0, rstate = 0, rlo = 0, rhi = 0, nhits = 0, gap = 0;
   uint32_t rubase = 0;
   float p[5], C[15], xc = 0.f;
   uint32_t iters = 0;
   int nupd = 0;   // Kalman updates of the current seed (the first three are compensated)
-  // the record of the next chain cluster (nxt), loaded one step ahead
+  // loaded one step ahead: the record of the next chain cluster (nxt), or
+  // the plane and grid of the next row r
   float4 cn = make_float4(0.f, 0.f, 0.f, 0.f);
-  // hit slots are written through a four-row buffer (rows are visited in
-  // order within a phase), one 16-byte store per full group of four rows
+  float Xr = 0.f;
+  GridParams Q{};
+  // hit slots: with one lane per seed they go through a four-row buffer
+  // (rows are visited in order within a phase), one 16-byte store per full
+  // group of four rows -- the wave's lanes store to 64 lines, and single
+  // stores cost the central event 60 us more; groups store each hit as it
+  // comes (few lanes store, and a step is 25 instructions shorter)
+  int32_t* hits = nullptr;   // the seed's slots of the first band
   int32_t wb0 = 0, wb1 = 0, wb2 = 0, wb3 = 0;
   int wbase = -1;
   uint32_t wmask = 0;
-  const int64_t bstride = (int64_t)w.seed_cap * 8;   // between the bands of one seed
+  auto slot = [&](int row) { return hits + ((int64_t)(row >> 3) * ((int64_t)w.seed_cap * 8) + (row & 7)); };
   auto flush = [&]() {
-    int32_t* q = hits + (int64_t)(wbase >> 3) * bstride + (wbase & 7);
+    int32_t* q = slot(wbase);
     if (wmask == 0xFu) {
       *(int4*)q = make_int4(wb0, wb1, wb2, wb3);
-    } else if (wmask) {
+    } else {
       if (wmask & 1u) q[0] = wb0;
       if (wmask & 2u) q[1] = wb1;
       if (wmask & 4u) q[2] = wb2;
@@ -1565,16 +1623,21 @@ __global__ __launch_bounds__(TB) void k_tracklets(Ws w) {
     wmask = 0;
   };
   auto put = [&](int row, int32_t v) {
-    const int b = row & ~3;
-    if (b != wbase) { flush(); wbase = b; }
-    const int q = row & 3;
-    // value selects, not a store through a selected pointer: the latter
-    // would put the buffer in scratch memory
-    wb0 = q == 0 ? v : wb0;
-    wb1 = q == 1 ? v : wb1;
-    wb2 = q == 2 ? v : wb2;
-    wb3 = q == 3 ? v : wb3;
-    wmask |= 1u << q;
+    if constexpr (G > 1) {
+      if (gl == 0) *slot(row) = v;
+    } else {
+      const int b = row & ~3;
+      if (b != wbase && wmask != 0u) flush();
+      wbase = b;
+      const int q = row & 3;
+      // value selects, not a store through a selected pointer: the latter
+      // would put the buffer in scratch memory
+      wb0 = q == 0 ? v : wb0;
+      wb1 = q == 1 ? v : wb1;
+      wb2 = q == 2 ? v : wb2;
+      wb3 = q == 3 ? v : wb3;
+      wmask |= 1u << q;
+    }
   };
   // seed range of this workgroup's XCD (workgroups are dispatched to the
   // XCDs round-robin), so that each XCD's L2 holds the grids of its sectors
@@ -1584,188 +1647,233 @@ __global__ __launch_bounds__(TB) void k_tracklets(Ws w) {
     // this cap is never reached by a correct kernel; it turns a defect into
     // an error instead of a hang
     if (++iters > (1u << 22)) { atomicOr(&w.flags[F_ERR], ERR_STUCK); break; }
-    // finished lanes publish their tracklet and take new seeds
-    if (phase == ST_DONE) {
-      flush();
-      wbase = -1;
-      float* st = w.tl_state + s * kTl;
-#pragma unroll
-      for (int i = 0; i < 5; ++i) st[i] = p[i];
-#pragma unroll
-      for (int i = 0; i < 15; ++i) st[5 + i] = C[i];
-      w.tl_nhits[s] = nhits;
-      w.tl_range[s] = rlo | (rhi << 16);
-      w.tl_key[s] = ((uint64_t)(uint32_t)nhits << 40) | ((uint64_t)(255 - r0) << 32) |
-                    (uint64_t)(0xFFFFFFFFu - w.cid[h0]);
-      phase = ST_IDLE;
-    }
-    bool want = phase == ST_IDLE && s != -2;
-    uint64_t wm = __ballot(want);
+    const uint64_t act = __ballot(phase < ST_DONE);
     // refills stall the whole wave (counter, atomic, seed set-up): take new
     // seeds only once a quarter of the lanes wait, or no lane is working
-    if (__popcll(wm) < kRefillMin && __ballot(phase != ST_IDLE) != 0ull) wm = 0ull;
-    while (wm) {
-      const uint32_t lo = (uint32_t)(((uint64_t)ns * (uint32_t)rx) / kXcd);
-      const uint32_t hi = (uint32_t)(((uint64_t)ns * (uint32_t)(rx + 1)) / kXcd);
-      uint32_t* ctr = &w.flags[F_SEEDCTR + rx];
-      // a fresh (L2-bypassing) read first: exhausted ranges cost no atomic
-      uint32_t base = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (base < hi - lo) {
-        const int leader = __ffsll((unsigned long long)wm) - 1;
-        if (lane_id() == leader) base = atomicAdd(ctr, (uint32_t)__popcll(wm));
-        base = __shfl(base, leader, 64);
-        if (want) {
-          const uint64_t mine = (uint64_t)lo + base + (uint32_t)__popcll(wm & lanemask_lt());
-          if (mine < hi) {
-            want = false;
-            s = (int64_t)mine;
-            h0 = (int32_t)w.seeds[s];
-            const uint32_t ru0 = w.cru[h0];
-            r0 = (int)(ru0 % (uint32_t)R);
-            rubase = ru0 - (uint32_t)r0;
-            hits = w.tl_hits + s * 8;
-            const float4 a0 = w.cpk[h0];
-            const int32_t h1 = __float_as_int(a0.w);
-            const float4 a1 = w.cpk[h1];
-            const int32_t h2 = __float_as_int(a1.w);
-            const float4 a2 = w.cpk[h2];
-            float sdir, tdir;
-            const float x0 = a0.x, y0 = a0.y, z0 = a0.z;
-            chord_dir(x0, y0, z0, a2.x, a2.y, a2.z, sdir, tdir);
-            p[0] = y0; p[1] = z0; p[2] = sdir; p[3] = tdir; p[4] = 0.0f;
-            init_cov(C, w.m.vy, w.m.vz);
-            nupd = 0;
-            rlo = rhi = rstate = r0;
-            xc = x0;
-            if (fabsf(sdir) < w.m.sin_max) {
-              put(r0, h0);
-              nhits = 1;
-              nxt = h1;
-              cn = a1;
-              phase = ST_CHAIN;
-            } else {
-              nhits = 0;
-              phase = ST_DONE;
+    if (act == 0ull || (more && 64 - __popcll(act) >= kRefillMin)) {
+      if (phase == ST_DONE) {
+        if (G == 1 && wmask) flush();
+        if (gl == 0) {
+          float* st = w.tl_state + (int64_t)s * kTl;
+#pragma unroll
+          for (int i = 0; i < 5; ++i) st[i] = p[i];
+#pragma unroll
+          for (int i = 0; i < 15; ++i) st[5 + i] = C[i];
+          w.tl_nhits[s] = nhits;
+          w.tl_range[s] = rlo | (rhi << 16);
+          w.tl_key[s] = ((uint64_t)(uint32_t)nhits << 40) | ((uint64_t)(255 - r0) << 32) |
+                        (uint64_t)(0xFFFFFFFFu - w.cid[h0]);
+        }
+        phase = ST_IDLE;
+      }
+      bool want = phase == ST_IDLE;
+      uint64_t wm = more ? __ballot(want) : 0ull;
+      while (wm) {
+        const uint32_t lo = (uint32_t)(((uint64_t)ns * (uint32_t)rx) / kXcd);
+        const uint32_t hi = (uint32_t)(((uint64_t)ns * (uint32_t)(rx + 1)) / kXcd);
+        uint32_t* ctr = &w.flags[F_SEEDCTR + rx];
+        // a fresh (L2-bypassing) read first: exhausted ranges cost no atomic
+        uint32_t base = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (base < hi - lo) {
+          const int leader = __ffsll((unsigned long long)wm) - 1;
+          if (lane_id() == leader) base = atomicAdd(ctr, (uint32_t)__popcll(wm) / G);
+          base = __shfl(base, leader, 64);
+          if (want) {
+            const uint64_t mine = (uint64_t)lo + base + (uint32_t)__popcll(wm & groups_before) / G;
+            if (mine < hi) {
+              want = false;
+              s = (uint32_t)mine;
+              h0 = (int32_t)w.seeds[s];
+              const uint32_t ru0 = w.cru[h0];
+              r0 = (int)(ru0 % (uint32_t)R);
+              rubase = ru0 - (uint32_t)r0;
+              const float4 a0 = w.cpk[h0];
+              const int32_t h1 = __float_as_int(a0.w);
+              const float4 a1 = w.cpk[h1];
+              const int32_t h2 = __float_as_int(a1.w);
+              const float4 a2 = w.cpk[h2];
+              float sdir, tdir;
+              const float x0 = a0.x, y0 = a0.y, z0 = a0.z;
+              chord_dir(x0, y0, z0, a2.x, a2.y, a2.z, sdir, tdir);
+              p[0] = y0; p[1] = z0; p[2] = sdir; p[3] = tdir; p[4] = 0.0f;
+              init_cov(C, w.m.vy, w.m.vz);
+              nupd = 0;
+              rlo = rhi = rstate = r0;
+              xc = x0;
+              hits = w.tl_hits + (int64_t)s * 8;
+              wbase = -1;
+              if (fabsf(sdir) < w.m.sin_max) {
+                put(r0, h0);
+                nhits = 1;
+                nxt = h1;
+                cn = a1;
+                phase = ST_CHAIN;
+              } else {
+                nhits = 0;
+                phase = ST_DONE;
+              }
             }
           }
         }
-      }
-      wm = __ballot(want);
-      if (wm) {
-        // this range is used up: take seeds from the next one
-        if (++tries >= kXcd) {
-          if (want) s = -2;   // every range is used up: no more work for this lane
-          break;
+        wm = __ballot(want);
+        if (wm) {
+          // this range is used up: take seeds from the next one
+          if (++tries >= kXcd) { more = false; break; }   // every range is used up
+          rx = (rx + 1) % kXcd;
         }
-        rx = (rx + 1) % kXcd;
       }
+      if (__ballot(phase != ST_IDLE) == 0ull) break;
     }
-    if (__ballot(phase != ST_IDLE) == 0ull) break;
-    if (phase == ST_DONE || phase == ST_IDLE) continue;
+    if (phase >= ST_DONE) continue;
     // one row step: every active lane transports once (the target plane
     // depends on the phase), then the phase's own work follows
     const bool chain = phase == ST_CHAIN;
-    const bool search = phase == ST_UP || phase == ST_DOWN;
-    float X, my = 0.0f, mz = 0.0f;
-    int32_t cnx = -1;
-    GridParams G;
-    if (chain) {
-      X = cn.x; my = cn.y; mz = cn.z; cnx = __float_as_int(cn.w);
-    } else {
-      X = sX[r];
-    }
-    if (search) G = w.grid[rubase + (uint32_t)r];
+    const float X = chain ? cn.x : Xr;
+    float my = cn.y, mz = cn.z;
     bool go = transport(p, C, xc, X, w.m);
-    bool upd = false, wrote = false;
+    bool upd = false, wr = false;
+    int prow = r;
+    int32_t pval = nxt;
+    // whether the lane's phase ends with this step (chain used up, no
+    // further row, too many rows without a cluster, a refused transport) or
+    // is on its way back: settled in one place below
+    bool turn;
     if (chain) {
-      upd = go;
-    } else if (search && go) {
-      xc = X;
-      rstate = r;
-      go = accepted(X, acc, p);
-      if (go) {
-        const Found h = search_row(w, G, p, C);
-        if (h.pos >= 0) {
-          float hx = X;
-          if (G.off_plane) hx = w.cx[h.pos];
-          if (hx != X) {
-            go = transport(p, C, X, hx, w.m);
-            if (go) xc = hx;
+      nxt = __float_as_int(cn.w);
+      wr = upd = go;
+      rstate += go ? 1 : 0;
+      nhits = go ? nhits + 1 : 0;
+      prow = rstate;
+      xc = go ? X : xc;
+      turn = !go || nxt < 0;
+    } else {
+      const bool back = phase == ST_BACK;
+      xc = go ? X : xc;
+      turn = back;
+      if (!back) {
+        rstate = go ? r : rstate;
+        go = go && accepted(X, acc, p);
+        if (go) {
+          const Found h = search_row<G>(w, Q, p, C, gl);
+          pval = h.pos;
+          my = h.y; mz = h.z;
+          upd = h.pos >= 0;
+          if (upd && h.x != X) {   // a cluster off its row's plane
+            upd = go = transport(p, C, X, h.x, w.m);
+            xc = go ? h.x : xc;
           }
-          if (go) {
-            my = h.y; mz = h.z;
-            upd = true;
-            put(r, h.pos);
-            ++nhits;
-            gap = 0;
-            wrote = true;
-          }
-        } else {
-          put(r, -1);
-          ++gap;
-          wrote = true;
+          wr = go;
+          nhits += upd ? 1 : 0;
+          gap = upd ? 0 : gap + 1;
+          go = go && gap <= w.P.max_gap;
         }
-        if (wrote) go = gap <= w.P.max_gap;
+        const bool up = phase == ST_UP;
+        rhi = wr && up ? r : rhi;
+        rlo = wr && !up ? r : rlo;
+        const int rn = up ? r + 1 : r - 1;
+        turn = !go || (uint32_t)rn >= (uint32_t)R;
+        r = turn ? r : rn;
       }
     }
+    if (turn) {
+      if (chain && !go) {
+        rlo = rhi = r0;
+        phase = ST_DONE;
+      } else if (phase == ST_DOWN || (phase == ST_BACK && !go)) {
+        phase = ST_DONE;
+      } else {
+        // the next row above the chain, the next stop on the way back to the
+        // first row, or the first row below it
+        if (chain) rhi = rstate;
+        gap = 0;
+        const int at = phase == ST_BACK ? r : rstate;
+        if (chain && at + 1 < R) {
+          r = at + 1;
+          phase = ST_UP;
+        } else if (at > r0 || chain) {
+          r = max(r0, at - kBackRows);
+          phase = ST_BACK;
+        } else {
+          r = r0 - 1;
+          phase = r >= 0 ? ST_DOWN : ST_DONE;
+        }
+      }
+    }
+    // the next step's inputs, in flight during the update
+    if (phase == ST_CHAIN) {
+      cn = w.cpk[nxt];
+    } else if (phase < ST_DONE) {
+      Xr = sX[r];
+      Q = w.grid[rubase + (uint32_t)r];
+    }
+    if (wr) put(prow, pval);
     if (upd) {
       float dummy = 0.0f;
       if (nupd < TPCCA_GRAD_C2_UPDATES) update_c2(p, C, my, mz, w.m, dummy);
       else update(p, C, my, mz, w.m, dummy);
       ++nupd;
     }
-    if (chain) {
-      if (!go) {
-        nhits = 0; rlo = rhi = r0; phase = ST_DONE;
-      } else {
-        ++rstate;
-        put(rstate, nxt);
-        ++nhits;
-        xc = X;
-        nxt = cnx;
-        if (nxt < 0) {
-          rhi = rstate;
-          gap = 0;
-          r = rstate + 1;
-          phase = r < R ? ST_UP : ST_BACK;
-          if (phase == ST_BACK) r = max(r0, rstate - kBackRows);
-        }
-      }
-    } else if (phase == ST_BACK) {
-      if (!go) {
-        phase = ST_DONE;
-      } else {
-        xc = X;
-        if (r == r0) {
-          gap = 0;
-          r = r0 - 1;
-          phase = r >= 0 ? ST_DOWN : ST_DONE;
-        } else {
-          r = max(r0, r - kBackRows);
-        }
-      }
-    } else if (phase == ST_UP) {
-      if (wrote) rhi = r;
-      if (go && r + 1 < R) {
-        ++r;
-      } else {
-        if (rstate > r0) {
-          r = max(r0, rstate - kBackRows);
-          phase = ST_BACK;
-        } else {
-          gap = 0;
-          r = r0 - 1;
-          phase = r >= 0 ? ST_DOWN : ST_DONE;
-        }
-      }
-    } else {
-      if (wrote) rlo = r;
-      if (go && r - 1 >= 0) --r; else phase = ST_DONE;
-    }
-    // the next chain record, loaded now so that it is there when the next
-    // step's transport needs its plane
-    if (phase == ST_CHAIN) cn = w.cpk[nxt];
   }
+}
+
+// Lanes per seed.  A launch with few seeds lasts as long as one seed's chain
+// of about 162 dependent steps, so lanes that would idle shorten the step:
+// with eight lanes a search is one load and a group minimum instead of four
+// to eight loads and tests in a row.  More lanes are more waves, each issuing
+// the whole step: the lines are one wave per SIMD at eight lanes (1024 SIMDs
+// x 64 / 8 seeds) and two at four.  Measured per launch with 1 / 4 / 8 lanes:
+// 2,337 seeds 445 / 334 / 296 us, 14,124 seeds 428 / 343 / 373, 28,188 seeds
+// 462 / 396 / 537, 65,263 seeds 490 / 574 / 1479 (two lanes were never the
+// best).
+constexpr uint32_t kSeeds8 = 8192, kSeeds4 = 32768;
+__device__ __forceinline__ int tracklet_lanes(uint32_t ns) { return ns <= kSeeds8 ? 8 : ns <= kSeeds4 ? 4 : 1; }
+
+// Reads one word of every 128-byte line of [p, p + bytes), the lines spread
+// over nt threads of which this is thread t.
+__device__ __forceinline__ void touch_lines(const void* p, int64_t bytes, int64_t t, int64_t nt) {
+  uint32_t acc = 0;
+  for (int64_t i = t * 128; i < bytes; i += nt * 128) acc |= *(const uint32_t*)((const char*)p + i);
+  asm volatile("" ::"v"(acc));   // (the loads are kept, the value is not used)
+}
+
+// Workgroups without seeds read the search data of their XCD's seed range
+// (grids, cell offsets, entries: written by the binning on any XCD), if it
+// fits the XCD's 4 MB L2 beside what else is there, so that the dependent
+// loads of the search steps find it in that L2 instead of behind it (a
+// sector's 17 k clusters: 339 -> 298 us).  kWarmGrid: launched at least, so
+// that even the smallest events have such workgroups on every XCD.
+constexpr int64_t kWarmBytes = (int64_t)3 << 20;
+constexpr unsigned kWarmGrid = 512;
+
+__global__ __launch_bounds__(TB) void k_tracklets(Ws w) {
+  __shared__ float sX[256];
+  for (int r = threadIdx.x; r < w.R; r += TB) sX[r] = w.row_x[r];
+  __syncthreads();
+  const uint32_t ns = w.flags[F_NSEEDS];
+  const int G = tracklet_lanes(ns);
+  // when the lanes of the lower workgroups already outnumber the seeds they
+  // take (and, by refills, finish) them all: this one has no seeds to take
+  const int64_t busy = ((int64_t)ns + TB / G - 1) / (TB / G);
+  if ((int64_t)blockIdx.x >= busy) {
+    const uint32_t x = blockIdx.x % kXcd;
+    const uint32_t lo = (uint32_t)(((uint64_t)ns * x) / kXcd), hi = (uint32_t)(((uint64_t)ns * (x + 1)) / kXcd);
+    if (lo >= hi) return;
+    const uint32_t u0 = w.cru[w.seeds[lo]] / (uint32_t)w.R * (uint32_t)w.R;
+    const uint32_t u1 = (w.cru[w.seeds[hi - 1]] / (uint32_t)w.R + 1u) * (uint32_t)w.R;
+    const int64_t c0 = w.ru_off[u0], c1 = w.ru_off[u1], k0 = w.cell_base[u0], k1 = w.cell_base[u1];
+    const int64_t bytes = (c1 - c0) * 16 + (k1 - k0) * 2 + (int64_t)(u1 - u0) * (int64_t)sizeof(GridParams);
+    if (bytes > kWarmBytes) return;
+    const int64_t b0 = (busy + kXcd - 1 - x) / kXcd;   // (first idle workgroup of this XCD, in its own numbering)
+    const int64_t nt = ((int64_t)(gridDim.x + kXcd - 1 - x) / kXcd - b0) * TB;
+    const int64_t t = ((int64_t)(blockIdx.x / kXcd) - b0) * TB + threadIdx.x;
+    touch_lines(w.grid + u0, (int64_t)(u1 - u0) * (int64_t)sizeof(GridParams), t, nt);
+    touch_lines(w.cell_off + k0, (k1 - k0) * 2, t, nt);
+    touch_lines(w.gbuf + c0, (c1 - c0) * 16, t, nt);
+    return;
+  }
+  if (G == 8) tracklets_wave<8>(w, sX, ns);
+  else if (G == 4) tracklets_wave<4>(w, sX, ns);
+  else tracklets_wave<1>(w, sX, ns);
 }
 
 // ----------------------------------------------------------- a6: selection
@@ -2086,7 +2194,7 @@ hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, uint
 // workgroups past the actual seed count leave at once), or the tuned value.
 unsigned tracklet_grid(const Ws& w) {
   if (w.tracklet_grid > 0) return (unsigned)w.tracklet_grid;
-  return blocks_for(w.seed_cap, 1 << 16);
+  return std::max(blocks_for(w.seed_cap, 1 << 16), kWarmGrid);
 }
 
 namespace {

@@ -415,3 +415,37 @@ def test_event_above_2_22_clusters(tracker, orc):
     ref = orc.track(big, precision=32, sector_mask=mask)
     compare(big, out, tl, ref, sectors=sectors)
     assert out.n_tracks > 0
+
+
+def _clumped_event():
+    """One sector of tracks with clumps of 60 clusters in less than a cell of
+    a row's grid, so that a tracklet search meets many candidates in one
+    range, on rows the tracks cross."""
+    ev = synth.make_event(seed=41, n_primaries=120, noise=0.01, single_sector=True)
+    rng = np.random.default_rng(42)
+    on = rng.choice(np.nonzero(ev.truth_track >= 0)[0], 40, replace=False)
+    patches = [(int(ev.row[i]), int(rng.integers(2, 61)), (float(ev.y[i]) - 0.3, float(ev.y[i]) + 0.3),
+                (float(ev.z[i]) - 0.4, float(ev.z[i]) + 0.4)) for i in on]
+    return _with_patches(ev, patches, seed=43)
+
+
+@pytest.mark.parametrize("seeds", [1, 8193, 32769])
+def test_tracklet_lanes_per_seed(tracker, orc, seeds):
+    """The tracklet kernel gives a seed eight lanes up to 8,192 seeds of a
+    call, four up to 32,768 and one above: the same event, alone and in
+    batches of enough copies for each, equals the oracle."""
+    ev = _clumped_event()
+    t = to_dev(ev)
+    out = tracker.track(*t, taps=True)
+    tl = tracker.debug_tracklets()
+    ns = len(tl["seed_start"])
+    ref = orc.track(ev, precision=32)
+    compare(ev, out, tl, ref)
+    copies = -(-seeds // ns)
+    print(f"[gpu] {copies} copies of {ns} seeds", flush=True)
+    batch = tracker.track_batch([t] * copies)
+    for e in (0, copies // 2, copies - 1):
+        compare(ev, batch[e], None, ref, check_taps=False)
+    for b in batch:
+        for k in ("hit_off", "hit_id", "p", "cov", "chi2", "k_prior"):
+            assert torch.equal(getattr(b, k), getattr(out, k)), k
