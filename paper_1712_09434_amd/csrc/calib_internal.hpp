@@ -31,6 +31,7 @@ struct CalWs {
   const float* cy;
   const float* cz;
   const uint8_t* csec;
+  float4* cpack;           // [NC] the clusters as (x, y, z, sector bits), or null (read from the four arrays)
   const float* dl;
   const float* tau;
   const float* map;
@@ -38,9 +39,9 @@ struct CalWs {
   float* hy;
   float* hz;
   float* gx;               // [H] dx-derivative of the step ending at the hit
-  float* gy;
+  float* gy;               // (not used: the correction leaves y as it is)
   float* gz;
-  float* gpt;              // [H] x-adjoint point terms (seed chord, vertex hop)
+  float* gpt;              // [H] x-adjoint point terms (seed chord, vertex hop), at a track's first, third and last hit
   float4* bva;             // [H] the four non-zero x-direction B-splines at the hit
   float4* bvb;             // [H] the four non-zero y/x-direction B-splines at the hit
   int32_t* bsp;            // [H] index of the first of each four: x in bits 0-7, y/x in 8-15
@@ -49,8 +50,8 @@ struct CalWs {
   int32_t* tflag;          // [T] 0 failed, 1 hits only, 2 with vertex terms
   int32_t* tndf;           // [T]
   int32_t* flag_out;       // [T] per-track status for the caller (may be null)
-  float* ckpt;             // [T][nck][20]
-  float* seg;              // [T][nseg][20]
+  float* ckpt;             // nck states of 20 floats per track (layout: Slots in tpcca_calib.hip)
+  float* seg;              // nseg states per track
   double* chunk;           // [nchunk][S*66 + 1]
   double* out;             // [S*66 + 1]: per sector (delta, tau, map[64]), then chi2
   double* g_dl;            // device gradient outputs [S], [S], [S][64]; null for host outputs

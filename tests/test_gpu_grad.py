@@ -180,3 +180,68 @@ def test_bad_hit_ids_rejected(setup):
                     ext_tgl=fit.ext_tgl, use_vertex=fit.use_vertex)
     with pytest.raises(TpccaError):
         trk.refit_grad(bad, torch.zeros(S * 66, device="cuda:0"))
+
+
+def take_tracks(fit, tracks):
+    """The FitTracks of the given tracks of `fit`, in that order."""
+    from paper_1712_09434_amd import FitTracks
+    off, ids = fit.hit_off.cpu().numpy(), fit.hit_id.cpu().numpy()
+    tracks = np.asarray(tracks)
+    n = off[tracks + 1] - off[tracks]
+    d = lambda a, dt: torch.from_numpy(np.ascontiguousarray(a).astype(dt)).cuda()
+    sel = torch.from_numpy(tracks).cuda()
+    return FitTracks(clusters=fit.clusters, hit_off=d(np.concatenate([[0], np.cumsum(n)]), np.int32),
+                     hit_id=d(np.concatenate([ids[off[t]:off[t + 1]] for t in tracks]), np.int32),
+                     k_prior=fit.k_prior[sel], ext_tgl=fit.ext_tgl[sel], use_vertex=fit.use_vertex[sel])
+
+
+def test_gradient_of_parts_adds_up(setup):
+    """Tracks are handled in blocks of 64, sums in chunks of 256, and calls
+    with enough hits read packed clusters: the gradient of 1,100 tracks
+    (packed) is the sum of those of parts of 1, 63, 64, 65, 128, 257 and the
+    rest (none packed).  Every track's terms are the same bits in each call,
+    so only the order of at most 1,100 FP64 additions differs: 1e-10 of the
+    largest component covers it by three orders."""
+    ev, trk, fit, cs, theta_star = setup
+    th = torch.from_numpy((0.5 * theta_star.flat()).astype(np.float32)).cuda()
+    n = 1100
+    whole = take_tracks(fit, np.arange(n))
+    c2, ndf, g, flag = trk.refit_grad(whole, th, flags=True)
+    assert whole.hit_id.numel() * 8 >= ev.n
+    parts, at = [], 0
+    for size in (1, 63, 64, 65, 128, 257, n - 578):
+        sub = take_tracks(fit, np.arange(at, at + size))
+        assert sub.hit_id.numel() * 8 < ev.n
+        parts.append(trk.refit_grad(sub, th, flags=True))
+        at += size
+    assert at == n
+    assert ndf == sum(p[1] for p in parts)
+    assert abs(c2 - sum(p[0] for p in parts)) <= 1e-12 * c2
+    assert torch.equal(flag, torch.cat([p[3] for p in parts]))
+    s = sum(p[2] for p in parts)
+    for sl in (slice(0, S), slice(S, 2 * S), slice(2 * S, 66 * S)):
+        assert float((g[sl] - s[sl]).abs().max()) <= 1e-10 * float(g[sl].abs().max())
+
+
+def test_gradient_with_more_sectors_than_one_group_of_sums(setup):
+    """The same tracks in a geometry of 72 sectors, of which every second one
+    is used: the sums of the two halves of the sectors are those of the 36."""
+    from paper_1712_09434_amd import FitTracks, Tracker
+    ev, trk, fit, cs, theta_star = setup
+    th = (0.5 * theta_star.flat()).astype(np.float32)
+    c2, ndf, g = trk.refit_grad(fit, torch.from_numpy(th).cuda())
+    wide = Tracker(ev.geom.row_x, float(ev.geom.tan_half_angle), float(ev.geom.z_max), float(ev.geom.bz), 72)
+    x, y, z, row, sec = fit.clusters
+    fit2 = FitTracks(clusters=(x, y, z, row, (sec * 2).contiguous()), hit_off=fit.hit_off, hit_id=fit.hit_id,
+                     k_prior=fit.k_prior, ext_tgl=fit.ext_tgl, use_vertex=fit.use_vertex)
+    th2 = np.zeros(72 * 66, np.float32)
+    at = 2 * np.arange(S)
+    idx = np.concatenate([at, 72 + at, (144 + at[:, None] * 64 + np.arange(64)).ravel()])
+    th2[idx] = th
+    d2, ndf2, g2 = wide.refit_grad(fit2, torch.from_numpy(th2).cuda())
+    wide.close()
+    assert (d2, ndf2) == (c2, ndf)
+    assert torch.equal(g2[torch.from_numpy(idx).cuda()], g)
+    rest = torch.ones(72 * 66, dtype=torch.bool)
+    rest[idx] = False
+    assert not torch.any(g2[rest.cuda()])
