@@ -2047,55 +2047,58 @@ __global__ __launch_bounds__(TB) void k_acc_list(Ws w) {
 
 // Final fit of every accepted tracklet (dense over the accepted list):
 // outermost owned hit first, direction from the chord to the hit two
-// positions inward, q/pT prior from following; the next hit's coordinates
-// are loaded while the current step computes.
-__global__ __launch_bounds__(TB) void k_refit(Ws w) {
+// positions inward, q/pT prior from following.  One lane per track: bound by
+// the chain of at most 158 dependent steps, about 270 instructions each (70 %
+// of its time is their issue).  The first steps, whose updates are
+// compensated (1,200 instructions), have a loop of their own, so that the
+// code of the others, unrolled by four, stays short (0.77 M clusters: 122 ->
+// 107 us with the shorter quotients, 24-collision frame 195 -> 154).
+__global__ __launch_bounds__(64) void k_refit(Ws w) {
   const uint32_t na = w.acc_off[w.seed_cap];
-  for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < na; i += (int64_t)gridDim.x * TB) {
+  for (int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x; i < na; i += (int64_t)gridDim.x * 64) {
     const int64_t s = w.acc_list[i];
     const int32_t* own = w.tl_own + s * w.R;
-    const uint32_t cnt = w.own_cnt[s];
+    const uint32_t cnt = w.own_cnt[s];   // (>= min_hits >= 3)
     float p[5], C[15], sdir, tdir;
-    const int32_t o0 = own[0], o2 = own[2];
-    const float4 c0 = w.cpk[o0], c2 = w.cpk[o2];
-    const float xo = c0.x, yo = c0.y, zo = c0.z;
-    chord_dir(c2.x, c2.y, c2.z, xo, yo, zo, sdir, tdir);
+    const int32_t o0 = own[0];
+    const float4 c0 = w.cpk[o0];
+    float4 c1 = w.cpk[own[1]], c2 = w.cpk[own[2]], c3 = w.cpk[3 < cnt ? own[3] : o0];
+    // hit records are read four steps ahead of their use and hit indices
+    // eight steps ahead, so loads overlap the filter steps: one register slot
+    // per step of the unrolled loop, refilled right after its use, and no
+    // register moves (which would wait for the loads in flight)
+    auto index = [&](uint32_t k) { return own[k < cnt ? k : 0u]; };   // (past the end: the first hit, never used)
+    constexpr uint32_t kc = TPCCA_GRAD_C2_UPDATES + 1;
+    float4 q0 = w.cpk[index(kc)], q1 = w.cpk[index(kc + 1)], q2 = w.cpk[index(kc + 2)], q3 = w.cpk[index(kc + 3)];
+    int32_t j0 = index(kc + 4), j1 = index(kc + 5), j2 = index(kc + 6), j3 = index(kc + 7);
+    chord_dir(c2.x, c2.y, c2.z, c0.x, c0.y, c0.z, sdir, tdir);
     const float kpr = w.tl_state[s * kTl + 4];
-    p[0] = yo; p[1] = zo; p[2] = sdir; p[3] = tdir; p[4] = kpr;
+    p[0] = c0.y; p[1] = c0.z; p[2] = sdir; p[3] = tdir; p[4] = kpr;
     init_cov(C, w.m.vy, w.m.vz);
     float chi2 = 0.0f;
     bool ok = fabsf(sdir) < w.m.sin_max;
-    float xc = xo;
-    // hit records are read four steps ahead of their use and hit indices
-    // eight steps ahead, so loads overlap the filter steps.  The loop is
-    // unrolled by four with one register slot per step: a slot is refilled
-    // right after its use, and no register moves (which would wait for the
-    // loads in flight) rotate the slots.
-    float4 q0 = w.cpk[own[1]];
-    float4 q1 = w.cpk[2 < cnt ? own[2] : o0];
-    float4 q2 = w.cpk[3 < cnt ? own[3] : o0];
-    float4 q3 = w.cpk[4 < cnt ? own[4] : o0];
-    int32_t j0 = own[5 < cnt ? 5u : 0u], j1 = own[6 < cnt ? 6u : 0u];
-    int32_t j2 = own[7 < cnt ? 7u : 0u], j3 = own[8 < cnt ? 8u : 0u];
-    // (past the list's end a slot is refilled from the first hit, never
-    // used: loads made by every step, whether its hit exists or not, leave
-    // no register to merge after them)
-    // The refill is issued after the step's arithmetic, when the slot's old
-    // value is dead, so it lands in the same registers.
+    float xc = c0.x;
+    for (uint32_t k = 1; ok && k < kc && k < cnt; ++k) {
+      ok = transport(p, C, xc, c1.x, w.m);
+      if (ok) {
+        update_c2(p, C, c1.y, c1.z, w.m, chi2);
+        xc = c1.x;
+      }
+      c1 = c2;
+      c2 = c3;
+    }
     auto step = [&](float4& q, int32_t& j, uint32_t k) {
       if (ok && k < cnt) {
-        if (transport(p, C, xc, q.x, w.m)) {
-          if (k <= (uint32_t)TPCCA_GRAD_C2_UPDATES) update_c2(p, C, q.y, q.z, w.m, chi2);
-          else update(p, C, q.y, q.z, w.m, chi2);
+        ok = transport(p, C, xc, q.x, w.m);
+        if (ok) {
+          update(p, C, q.y, q.z, w.m, chi2);
           xc = q.x;
-        } else {
-          ok = false;
         }
       }
-      q = w.cpk[k + 4 < cnt ? j : o0];
-      j = own[k + 8 < cnt ? k + 8 : 0u];
+      q = w.cpk[j];
+      j = index(k + 8);
     };
-    for (uint32_t k = 1; ok && k < cnt; k += 4) {
+    for (uint32_t k = kc; ok && k < cnt; k += 4) {
       step(q0, j0, k);
       step(q1, j1, k + 1);
       step(q2, j2, k + 2);
@@ -2283,7 +2286,7 @@ hipError_t run_pipeline(const Ws& w, hipStream_t st, const PhaseEvents* pe) {
   k_accept<<<xcd_blocks(w.seed_cap * 32), TB, 0, st>>>(w);
   TPCCA_CHECK(scan_u32(w.acc_flag, w.acc_off, w.seed_cap, w.scan_tmp, st));
   k_acc_list<<<blocks_for(w.seed_cap, 4096), TB, 0, st>>>(w);
-  k_refit<<<blocks_for(w.seed_cap / 4 + 1, 4096), TB, 0, st>>>(w);
+  k_refit<<<blocks_for(w.seed_cap + 1, 16384), 64, 0, st>>>(w);
   TPCCA_MARK(PH_OUTPUT);
   // track offsets (indicator of a fitted track) and hit offsets (owned
   // count) from the owned counts, by the same launches

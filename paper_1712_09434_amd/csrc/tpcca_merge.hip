@@ -47,37 +47,31 @@ __device__ bool rotate_state(float& x, float p[5], float C[15], float ca, float 
   if (!(fabsf(s2) < m.sin_max)) return false;
   const float c2 = sqrtf(fmaf(-s2, s2, 1.0f));
   const float kap = m.kfac * p[4];
-  float J[5][5];
-#pragma unroll
-  for (int i = 0; i < 5; ++i)
-#pragma unroll
-    for (int j = 0; j < 5; ++j) J[i][j] = i == j ? 1.0f : 0.0f;
-  J[0][0] = ca - (s2 / c2) * sa;
-  J[1][0] = -(p[3] / c2) * sa;
-  J[2][0] = -kap * sa;
-  J[2][2] = ca + sa * (s / c);
-  float T[5][5];
-#pragma unroll
-  for (int i = 0; i < 5; ++i)
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-      float acc = 0.0f;
-#pragma unroll
-      for (int k = 0; k < 5; ++k) acc += J[i][k] * C[sym(k, j)];
-      T[i][j] = acc;
-    }
-  float Cn[15];
-#pragma unroll
-  for (int i = 0; i < 5; ++i)
-#pragma unroll
-    for (int j = i; j < 5; ++j) {
-      float acc = 0.0f;
-#pragma unroll
-      for (int k = 0; k < 5; ++k) acc += T[i][k] * J[j][k];
-      Cn[sym(i, j)] = acc;
-    }
-#pragma unroll
-  for (int i = 0; i < 15; ++i) C[i] = Cn[i];
+  // J C J^T, the terms of J that are not 0 or 1 only, in the order of the
+  // full sums (45 operations instead of 400: some lane of a wave crosses a
+  // boundary at nearly every step of the merged refit; with the refit's loops
+  // 188 -> 149 us on 12 k chains, the pair search 86 -> 64)
+  const float j00 = ca - (s2 / c2) * sa;
+  const float j10 = -(p[3] / c2) * sa;
+  const float j20 = -kap * sa;
+  const float j22 = ca + sa * (s / c);
+  const float T00 = j00 * C[0], T01 = j00 * C[1], T02 = j00 * C[2];
+  const float T10 = j10 * C[0] + C[1], T11 = j10 * C[1] + C[5], T12 = j10 * C[2] + C[6];
+  const float T13 = j10 * C[3] + C[7], T14 = j10 * C[4] + C[8];
+  const float T20 = j20 * C[0] + j22 * C[2], T22 = j20 * C[2] + j22 * C[9];
+  const float T23 = j20 * C[3] + j22 * C[10], T24 = j20 * C[4] + j22 * C[11];
+  C[3] = j00 * C[3];
+  C[4] = j00 * C[4];
+  C[0] = T00 * j00;
+  C[1] = T00 * j10 + T01;
+  C[2] = T00 * j20 + T02 * j22;
+  C[5] = T10 * j10 + T11;
+  C[6] = T10 * j20 + T12 * j22;
+  C[7] = T13;
+  C[8] = T14;
+  C[9] = T20 * j20 + T22 * j22;
+  C[10] = T23;
+  C[11] = T24;
   const float x2 = x * ca + p[0] * sa;
   p[0] = -(x * sa) + p[0] * ca;
   p[2] = s2;
@@ -509,46 +503,55 @@ __global__ __launch_bounds__(64) void k_mrg_refit(MergeWs w) {
   init_cov(C, m.vy, m.vz);
   float chi2 = 0.0f, xc = r0.x;
   bool ok = fabsf(s) < m.sin_max;
-  int nupd = 0;
+  // entering the next inner segment (its frame, unless it lies in the same
+  // sector: a neighbouring slice of a time frame)
+  auto enter = [&]() {
+    const int wc = sec_c % w.NW, wa = sec_a % w.NW;
+    if (sec_a != sec_c && !rotate_state(xc, p, C, w.ca, turn_sign(wc, wa, w.NW) * w.sa, m)) ok = false;
+    c = na;
+    sec_c = sec_a;
+    seg_lo -= len_a;
+    na = nna;
+    sa = na >= 0 ? na : c;
+    sec_a = w.sector[sa];
+    len_a = w.hit_off[sa + 1] - w.hit_off[sa];
+    nna = w.inner[sa];
+  };
   auto at = [&](int32_t k) { return k >= 0 ? k : 0; };
-  // ring slots: coordinates of hits k, k-1, k-2, k-3; ids of hits k-4 .. k-7
-  int32_t k = n - 2;
-  float4 c0 = X(ids[at(k)]), c1 = X(ids[at(k - 1)]), c2 = X(ids[at(k - 2)]), c3 = X(ids[at(k - 3)]);
-  uint32_t j0 = ids[at(k - 4)], j1 = ids[at(k - 5)], j2 = ids[at(k - 6)], j3 = ids[at(k - 7)];
-  auto step = [&](float4& cs, uint32_t& js) {
+  // ring slots of the unrolled loop: coordinates of hits k0 .. k0-3, ids of
+  // hits k0-4 .. k0-7; the compensated steps before them (hits n-2 and on)
+  // in a loop of their own, as in the final fit
+  const int32_t k0 = n - 2 - (int32_t)TPCCA_GRAD_C2_UPDATES;
+  float4 c0 = X(ids[at(k0)]), c1 = X(ids[at(k0 - 1)]), c2 = X(ids[at(k0 - 2)]), c3 = X(ids[at(k0 - 3)]);
+  uint32_t j0 = ids[at(k0 - 4)], j1 = ids[at(k0 - 5)], j2 = ids[at(k0 - 6)], j3 = ids[at(k0 - 7)];
+  float4 f0 = X(ids[n - 2]), f1 = r2, f2 = X(ids[at(n - 4)]);
+  for (int32_t k = n - 2; ok && k > k0 && k >= 0; --k) {
+    if (k < seg_lo) enter();
+    if (ok) ok = transport(p, C, xc, f0.x, m);
+    if (ok) {
+      update_c2(p, C, f0.y, f0.z, m, chi2);
+      xc = f0.x;
+    }
+    f0 = f1;
+    f1 = f2;
+  }
+  auto step = [&](float4& cs, uint32_t& js, int32_t k) {
     if (ok && k >= 0) {
-      if (k < seg_lo) {
-        // entering the next inner segment (its frame, unless it lies in the
-        // same sector: a neighbouring slice of a time frame)
-        const int wc = sec_c % w.NW, wa = sec_a % w.NW;
-        if (sec_a != sec_c && !rotate_state(xc, p, C, w.ca, turn_sign(wc, wa, w.NW) * w.sa, m))
-          ok = false;
-        c = na;
-        sec_c = sec_a;
-        seg_lo -= len_a;
-        na = nna;
-        sa = na >= 0 ? na : c;
-        sec_a = w.sector[sa];
-        len_a = w.hit_off[sa + 1] - w.hit_off[sa];
-        nna = w.inner[sa];
-      }
-      if (ok && !transport(p, C, xc, cs.x, m)) ok = false;
+      if (k < seg_lo) enter();
+      if (ok) ok = transport(p, C, xc, cs.x, m);
       if (ok) {
-        if (nupd < TPCCA_GRAD_C2_UPDATES) update_c2(p, C, cs.y, cs.z, m, chi2);
-        else update(p, C, cs.y, cs.z, m, chi2);
-        ++nupd;
+        update(p, C, cs.y, cs.z, m, chi2);
         xc = cs.x;
       }
     }
     cs = X(js);
     js = ids[at(k - 8)];
-    --k;
   };
-  while (ok && k >= 0) {
-    step(c0, j0);
-    step(c1, j1);
-    step(c2, j2);
-    step(c3, j3);
+  for (int32_t k = k0; ok && k >= 0; k -= 4) {
+    step(c0, j0, k);
+    step(c1, j1, k - 1);
+    step(c2, j2, k - 2);
+    step(c3, j3, k - 3);
   }
   if (ok) {
     w.emit[i] = 1u;
