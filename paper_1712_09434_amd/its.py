@@ -9,10 +9,18 @@ import ctypes as C
 from dataclasses import dataclass
 from typing import Optional
 
+import numpy as np
 import torch
 
 from . import _abi as A
-from .tracker import _ptr, _stream_handle
+from .tracker import _ptr, _stream_handle, pieces, struct_dtype, struct_ptr, used_pieces
+
+# per-tracklet arrays: type and values per tracklet
+_FIELDS = {k: (torch.float32 if k in ("chi2", "out_x", "out_p", "out_cov", "in_p", "in_cov") else torch.int32,
+               {"cls": (6,), "out_p": (5,), "out_cov": (15,), "in_p": (5,), "in_cov": (15,)}.get(k, ()))
+           for k in A.ITS_TRACK_ARRAYS}
+_CLUSTERS_DT = struct_dtype(A.tpcca_its_clusters)
+_TRACKS_DT = struct_dtype(A.tpcca_its_tracks)
 
 
 def _check(L, ctx, rc):
@@ -89,15 +97,10 @@ class ItsTracker:
         keep = [t.contiguous() for t in (x, y, z, layer, stave)]
         cl.x, cl.y, cl.z, cl.layer, cl.stave = (_ptr(t) for t in keep)
         cl.stream = _stream_handle(dev)
-        cap = max(int((layer == 0).sum().item()), 1)
-        i32 = dict(dtype=torch.int32, device=dev)
-        f32 = dict(dtype=torch.float32, device=dev)
-        o = dict(tl0=torch.empty(cap, **i32), tl1=torch.empty(cap, **i32), ok=torch.empty(cap, **i32),
-                 cls=torch.empty(cap, 6, **i32), ncls=torch.empty(cap, **i32), chi2=torch.empty(cap, **f32),
-                 out_layer=torch.empty(cap, **i32), out_stave=torch.empty(cap, **i32), out_x=torch.empty(cap, **f32),
-                 out_p=torch.empty(cap, 5, **f32), out_cov=torch.empty(cap, 15, **f32),
-                 in_ok=torch.empty(cap, **i32), in_stave=torch.empty(cap, **i32), in_p=torch.empty(cap, 5, **f32),
-                 in_cov=torch.empty(cap, 15, **f32))
+        # one entry per cluster (the tracklets are at most the layer-0 clusters;
+        # counting those would wait for the device)
+        cap = max(cl.n, 1)
+        o = {k: torch.empty((cap, *shape), dtype=dtype, device=dev) for k, (dtype, shape) in _FIELDS.items()}
         h = torch.empty(self.nbins, dtype=torch.int32, device=dev) if hist else None
         st = A.tpcca_its_tracks()
         st.cap = cap
@@ -122,15 +125,55 @@ class ItsTracker:
     def prepare_batch(self, events, hist: bool = False):
         """Marshals a batch once (output tensors, structs) and returns
         run(results=True): one tpcca_its_track_batch call on it, for repeated
-        calls on the same inputs."""
-        ev = [self._event(*e, hist) for e in events]
-        n = len(ev)
-        cls = (A.tpcca_its_clusters * max(n, 1))(*[e[0] for e in ev])
-        sts = (A.tpcca_its_tracks * max(n, 1))(*[e[1] for e in ev])
+        calls on the same inputs.  The result tensors of the events are slices
+        of one array per field."""
+        E = len(events)
+        if E == 0:
+            return lambda results=True: []
+        dev = events[0][0].device
+        if any(e[0].device != dev for e in events):
+            return self._prepare_apart(events, hist)
+        stream = _stream_handle(dev)
+        stream = (stream.value or 0) if stream is not None else 0
+        keep = [[t.contiguous() for t in e] for e in events]
+        cls = np.array([(e[0].shape[0], *(t.data_ptr() for t in e), stream) for e in keep], dtype=_CLUSTERS_DT)
+        cap = np.maximum(cls["n"], 1)
+        size, at = pieces(cap)
+        total = int(size.sum())
+        o = {k: torch.empty((total, *shape), dtype=dtype, device=dev) for k, (dtype, shape) in _FIELDS.items()}
+        h = torch.empty(E, self.nbins, dtype=torch.int32, device=dev) if hist else None
+        sts = np.zeros(E, _TRACKS_DT)
+        sts["cap"] = cap
+        for k, v in o.items():
+            sts[k] = v.data_ptr() + v[0].numel() * 4 * at
+        if hist:
+            sts["hist"] = h.data_ptr() + 4 * self.nbins * np.arange(E)
 
         def run(results: bool = True):
-            if n == 0:
-                return []
+            _check(self.L, self.ctx, self.L.tpcca_its_track_batch(self.ctx, len(keep),
+                                                                  struct_ptr(cls, A.tpcca_its_clusters),
+                                                                  struct_ptr(sts, A.tpcca_its_tracks)))
+            if not results:
+                return None
+            n = sts["n_tracklets"]
+            cut = zip(*(used_pieces(v, n, size) for v in o.values()))
+            hs = h.unbind(0) if hist else [None] * E
+            col = [sts[k].tolist() for k in ("n_pairs", "peak", "vz_ok", "vz", "vfit_ok", "vfit_n", "vertex",
+                                             "vfit_sumw")]
+            return [ItsResult(**dict(zip(o, f)), hist=hh, n_pairs=a, peak=b, vz_ok=bool(c), vz=d, vfit_ok=bool(e),
+                              vfit_n=g, vertex=tuple(v), vfit_sumw=w)
+                    for f, hh, a, b, c, d, e, g, v, w in zip(cut, hs, *col)]
+        return run
+
+    def _prepare_apart(self, events, hist: bool):
+        """prepare_batch with each event's outputs in tensors of its own
+        (events on several devices)."""
+        ev = [self._event(*e, hist) for e in events]
+        n = len(ev)
+        cls = (A.tpcca_its_clusters * n)(*[e[0] for e in ev])
+        sts = (A.tpcca_its_tracks * n)(*[e[1] for e in ev])
+
+        def run(results: bool = True):
             _check(self.L, self.ctx, self.L.tpcca_its_track_batch(self.ctx, n, cls, sts))
             return [self._result(sts[i], e[2], e[3]) for i, e in enumerate(ev)] if results else None
         return run

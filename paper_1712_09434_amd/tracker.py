@@ -33,6 +33,45 @@ def _stream_handle(device: torch.device):
     return C.c_void_p(torch.cuda.current_stream(device).cuda_stream)
 
 
+def struct_dtype(struct) -> np.dtype:
+    """The numpy layout of a ctypes structure (pointers as integers), to fill
+    and read arrays of it by column."""
+    names, formats, offsets = [], [], []
+    for name, t in struct._fields_:
+        names.append(name)
+        if t is C.c_void_p or issubclass(t, C._Pointer):
+            t = np.uint64
+        elif issubclass(t, C.Array):
+            t = (np.dtype(t._type_), (t._length_,))
+        formats.append(t)
+        offsets.append(getattr(struct, name).offset)
+    return np.dtype(dict(names=names, formats=formats, offsets=offsets, itemsize=C.sizeof(struct)))
+
+
+def struct_ptr(a: np.ndarray, struct):
+    return C.cast(a.ctypes.data, C.POINTER(struct))
+
+
+def pieces(caps: np.ndarray):
+    """Consecutive pieces of one array that hold caps[e] entries each: their
+    sizes and where each begins.  Multiples of 16 entries, so that a piece of
+    any type begins on 16 bytes, as a tensor of its own would."""
+    sizes = (caps + 15) & ~15
+    return sizes, np.cumsum(sizes) - sizes
+
+
+def used_pieces(t: torch.Tensor, used: np.ndarray, sizes: np.ndarray):
+    """The first used[e] rows of each of the pieces of t."""
+    cuts = np.empty(2 * len(sizes), np.int64)
+    cuts[0::2] = used
+    cuts[1::2] = sizes - used
+    return t.split_with_sizes(cuts.tolist())[0::2]
+
+
+_CLUSTERS_DT = struct_dtype(A.tpcca_clusters)
+_TRACKS_DT = struct_dtype(A.tpcca_tracks)
+
+
 @dataclass
 class Tracks:
     """Tracks of one event (tensors on the input's device, already sliced to
@@ -246,6 +285,55 @@ class Tracker:
         return merged, seg, sl[:T], lk[:T]
 
     def track_batch(self, events: Sequence[tuple], taps: bool = False) -> List[Tracks]:
+        """Tracks of every event.  The tensors of the events are slices of one
+        array per field, shared by the events of the call (clone those of an
+        event to keep it without the others)."""
+        E = len(events)
+        dev = events[0][0].device if E else None
+        if E == 0 or taps or any(e[0].device != dev for e in events):
+            return self._track_batch_apart(events, taps)
+        # The structures as numpy columns and one allocation per field: with
+        # each event's structures filled field by field and nine allocations
+        # per event, 64 small events took 5.97 ms (3.2 of them the kernels),
+        # this way 4.46; seven 986 us, this way 880.
+        mem = A.TPCCA_MEM_DEVICE if dev.type == "cuda" else A.TPCCA_MEM_HOST
+        stream = _stream_handle(dev)
+        stream = (stream.value or 0) if stream is not None else 0
+        rows = []
+        for x, y, z, row, sector in events:
+            if not (x.is_contiguous() and y.is_contiguous() and z.is_contiguous() and row.is_contiguous()
+                    and sector.is_contiguous()):
+                raise ValueError("cluster arrays must be contiguous")
+            assert x.dtype == torch.float32 and row.dtype == torch.int16 and sector.dtype == torch.uint8
+            rows.append((x.shape[0], x.data_ptr(), y.data_ptr(), z.data_ptr(), row.data_ptr(), sector.data_ptr(),
+                         mem, stream))
+        cls = np.array(rows, dtype=_CLUSTERS_DT)
+        n = cls["n"]
+        cap_t = n // max(self.get_params().min_hits, 1) + 1
+        cap_h = np.maximum(n, 1)
+        size_t, at_t = pieces(cap_t + 1)  # hit_off has one entry more than the others
+        size_h, at_h = pieces(cap_h)
+        T, H = int(size_t.sum()), int(size_h.sum())
+        e = lambda dtype, *shape: torch.empty(shape, dtype=dtype, device=dev)
+        f32, i32 = torch.float32, torch.int32
+        o = dict(sector=e(torch.uint8, T), x_ref=e(f32, T), p=e(f32, T, 5), cov=e(f32, T, 15), chi2=e(f32, T),
+                 ndf=e(i32, T), k_prior=e(f32, T), hit_off=e(i32, T), hit_id=e(i32, H))
+        sts = np.zeros(E, _TRACKS_DT)
+        sts["cap_tracks"], sts["cap_hits"], sts["mem"] = cap_t, cap_h, mem
+        for k, bytes_per in (("sector", 1), ("x_ref", 4), ("p", 20), ("cov", 60), ("chi2", 4), ("ndf", 4),
+                             ("k_prior", 4), ("hit_off", 4)):
+            sts[k] = o[k].data_ptr() + bytes_per * at_t
+        sts["hit_id"] = o["hit_id"].data_ptr() + 4 * at_h
+        _check(self.L, self.ctx, self.L.tpcca_track_batch(self.ctx, E, struct_ptr(cls, A.tpcca_clusters),
+                                                          struct_ptr(sts, A.tpcca_tracks)))
+        nt = sts["n_tracks"]
+        cut = [used_pieces(o["hit_id"], sts["n_hits"], size_h) if k == "hit_id" else
+               used_pieces(v, nt + (k == "hit_off"), size_t) for k, v in o.items()]
+        return [Tracks(**dict(zip(o, f))) for f in zip(*cut)]
+
+    def _track_batch_apart(self, events: Sequence[tuple], taps: bool) -> List[Tracks]:
+        """track_batch with each event's outputs in tensors of its own (taps,
+        events on several devices)."""
         E = len(events)
         cls = (A.tpcca_clusters * E)()
         sts = (A.tpcca_tracks * E)()

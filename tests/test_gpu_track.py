@@ -449,3 +449,23 @@ def test_tracklet_lanes_per_seed(tracker, orc, seeds):
     for b in batch:
         for k in ("hit_off", "hit_id", "p", "cov", "chi2", "k_prior"):
             assert torch.equal(getattr(b, k), getattr(out, k)), k
+
+
+@pytest.mark.parametrize("dev", ["cuda:0", "cpu"])
+def test_batch_in_shared_arrays_equals_events_apart(tracker, dev):
+    """Batches without taps write slices of arrays shared by the events (each
+    beginning on 16 bytes); the events' own arrays hold the same."""
+    from paper_1712_09434_amd import TpccaError
+    evs = [to_dev(e, dev) for e in (synth.make_config("C1"), synth.make_event(seed=6, n_primaries=300, noise=0.05),
+                                    synth.make_event(seed=7, n_primaries=3, single_sector=True))]
+    one = evs[0]
+    evs[1:1] = [tuple(t[:0] for t in one), tuple(t[:1] for t in one)]
+    together = tracker.track_batch(evs)
+    apart = tracker._track_batch_apart(evs, False)
+    with pytest.raises(TpccaError):
+        tracker.track_batch([])   # refused, as by the library
+    for e, (a, b) in enumerate(zip(together, apart)):
+        for k in ("sector", "x_ref", "p", "cov", "chi2", "ndf", "k_prior", "hit_off", "hit_id"):
+            ta, tb = getattr(a, k), getattr(b, k)
+            assert ta.is_contiguous() and torch.equal(ta, tb), (e, k)
+            assert ta.numel() == 0 or ta.data_ptr() % 16 == 0, (e, k)
