@@ -31,13 +31,26 @@ constexpr int kRefillMin = 16;  // waiting lanes that make a wave take new seeds
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xF, 0xF, true);
+}
+template <int kCtrl>
+__device__ __forceinline__ float dpp_f32(float v) { return __uint_as_float(dpp_u32<kCtrl>(__float_as_uint(v))); }
+// Lane exchanges inside groups of two, four and eight lanes (the last one
+// mirrors the eight: enough once each four hold one value).
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppMirror8 = 0x141;
+constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128;   // rotations inside rows of 16 lanes
+
+// Row shifts inside 16 lanes, then the last lane of a row (of the first two
+// rows) to the rows behind it: six adds, no LDS crossbar.
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    uint32_t t = __shfl_up(v, d, 64);
-    if (lane >= d) v += t;
-  }
+  v += dpp_u32<0x111>(v);
+  v += dpp_u32<0x112>(v);
+  v += dpp_u32<0x114>(v);
+  v += dpp_u32<0x118>(v);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
   return v;
 }
 
@@ -469,30 +482,30 @@ __device__ __forceinline__ uint32_t cell_of(const GridParams& G, float y, float 
 
 // Search grid of a row unit of n clusters with the given bounding box: about
 // grid_cells(n) cells of equal shape over the box (one cell if the box is
-// degenerate or n < 4).
+// degenerate or n < 4).  The grid only bounds what a search visits, so
+// hardware reciprocals and roots (1 ulp) do; nz ny <= cap holds as a
+// quotient of integers up to kMaxCells that is not an integer lies further
+// than a few ulp below the next one.
 __device__ __forceinline__ GridParams make_grid(uint32_t n, uint32_t cbase, uint32_t off, float ymin, float ymax,
                                                 float zmin, float zmax) {
   const uint32_t cap = grid_cells(n);
-  uint32_t nz = 1, ny = 1;
+  const float fcap = (float)cap;
+  float nz = 1.0f, ny = 1.0f;
   float dz = zmax - zmin, dy = ymax - ymin;
   if (!(n > 0)) { zmin = 0.f; ymin = 0.f; dz = 0.f; dy = 0.f; }
   if (n >= 4 && dz > 0.0f && dy > 0.0f) {
-    const float a = sqrtf((dz * dy) / (float)cap);
-    nz = (uint32_t)fminf(fmaxf(dz / a, 1.0f), (float)cap);
-    ny = (uint32_t)fminf(fmaxf(dy / a, 1.0f), (float)(cap / nz));
+    const float ia = __builtin_amdgcn_rsqf((dz * dy) * __builtin_amdgcn_rcpf(fcap));   // 1 / cell edge
+    nz = floorf(fminf(fmaxf(dz * ia, 1.0f), fcap));
+    ny = floorf(fmaxf(fminf(dy * ia, fcap * __builtin_amdgcn_rcpf(nz)), 1.0f));
   }
   GridParams G;
-  G.cell_base = cbase; G.base = off; G.dims = GridParams::pack(nz, ny); G.pad = 0u;
+  G.cell_base = cbase; G.base = off; G.dims = GridParams::pack((uint32_t)nz, (uint32_t)ny); G.pad = 0u;
   G.z0 = zmin; G.y0 = ymin;
-  G.inv_bz = dz > 0.0f ? (float)nz / dz : 0.0f;
-  G.inv_by = dy > 0.0f ? (float)ny / dy : 0.0f;
+  G.inv_bz = dz > 0.0f ? nz * __builtin_amdgcn_rcpf(dz) : 0.0f;
+  G.inv_by = dy > 0.0f ? ny * __builtin_amdgcn_rcpf(dy) : 0.0f;
   return G;
 }
 
-// One block per row unit: the row unit's (x, y, z, id) entries sorted by id
-// in LDS (bitonic on the ids, carrying the entry's slot), canonical SoA
-// written in that order, then a uniform 2-D grid over the row's bounding box
-// with about two clusters per cell, filled by an LDS counting sort.
 // Ordering of LDS accesses between the lanes of one wave (the wave's LDS
 // operations complete in order; this waits for them and keeps the compiler
 // from moving accesses across).
@@ -502,13 +515,141 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Minima over the wave of four values a lane (returned to every lane as x,
+// y, z, w): two exchanges leave one value per lane, by its two low bits,
+// four more finish it.
+__device__ __forceinline__ float4 wave_min4(float a, float b, float c, float d) {
+  const bool o1 = threadIdx.x & 1, o2 = threadIdx.x & 2;
+  const float ab = fminf(o1 ? b : a, dpp_f32<kDppXor1>(o1 ? a : b));
+  const float cd = fminf(o1 ? d : c, dpp_f32<kDppXor1>(o1 ? c : d));
+  float v = fminf(o2 ? cd : ab, dpp_f32<kDppXor2>(o2 ? ab : cd));
+  v = fminf(v, dpp_f32<kDppRor4>(v));
+  v = fminf(v, dpp_f32<kDppRor8>(v));
+  v = fminf(v, __shfl_xor(v, 16, 64));
+  v = fminf(v, __shfl_xor(v, 32, 64));
+  auto at = [&](int l) { return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), l)); };
+  return make_float4(at(0), at(1), at(2), at(3));
+}
+
+__device__ __forceinline__ uint2 wave_min2(uint32_t a, uint32_t b) {
+  const bool o1 = threadIdx.x & 1;
+  uint32_t v = min(o1 ? b : a, dpp_u32<kDppXor1>(o1 ? a : b));
+  v = min(v, dpp_u32<kDppXor2>(v));
+  v = min(v, dpp_u32<kDppRor4>(v));
+  v = min(v, dpp_u32<kDppRor8>(v));
+  v = min(v, (uint32_t)__shfl_xor((int)v, 16, 64));
+  v = min(v, (uint32_t)__shfl_xor((int)v, 32, 64));
+  return make_uint2((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 1));
+}
+
+// Sorting the ids of a row unit.  They are distinct, so an entry's place is
+// the number of smaller ids.  Up to 64 entries count over all of them; in
+// larger units NT threads of four entries put the ids into 4 NT buckets over
+// equal ranges between the least and the largest id and count over their own
+// bucket: the ids of a row are spread evenly over the event's (or follow
+// each other if the input is sorted), so it holds one or two.  Where one
+// holds more than kBucketMax (clumped ids), every bucket of c ids is divided
+// again, into c buckets between its own least and largest id, up to three
+// times; a bucket that is still full takes longer and gives the same places.
+// Against a bitonic network over lanes and LDS: k_rows on a 3.8 M cluster
+// event 161 -> 45 us, ids in two clumps 162 -> 80, k_rows_wave and
+// k_rows_tiny on 64 small events 179 -> 81 and 303 -> 193.
+constexpr uint32_t kBucketMax = 24;
+
+// hist: 4 NT + 1 words, the first 4 NT cleared; list: 4 NT words; bnd: 8 NT
+// words.  place[k]: the place of K[k] where in[k].
+template <int NT>
+__device__ __forceinline__ void id_places(const uint32_t K[4], const bool in[4], uint32_t n, uint32_t kmin,
+                                          uint32_t kmax, uint32_t* hist, uint32_t* list, uint32_t* bnd,
+                                          uint32_t place[4]) {
+  const uint32_t t = threadIdx.x % NT;
+  auto sync = [] { if (NT == 64) wave_sync(); else __syncthreads(); };
+  uint32_t bk[4], arr[4], st[4], en[4], m;
+  const float scale = (float)(4 * NT) * __builtin_amdgcn_rcpf((float)(kmax - kmin) + 1.0f);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) bk[k] = min((uint32_t)((float)(K[k] - kmin) * scale), 4u * NT - 1u);
+  for (int level = 0;; ++level) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) arr[k] = in[k] ? atomicAdd(&hist[bk[k]], 1u) : 0u;
+    sync();
+    const uint4 h = ((const uint4*)hist)[t];
+    const uint32_t sum = h.x + h.y + h.z + h.w;
+    uint32_t e, tot;
+    if constexpr (NT == 64) e = wave_incl_scan(sum) - sum;
+    else e = block_excl_scan(sum, &tot);
+    ((uint4*)hist)[t] = make_uint4(e, e + h.x, e + h.x + h.y, e + h.x + h.y + h.z);
+    if (t == 0) hist[4 * NT] = n;
+    sync();
+    m = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      st[k] = hist[bk[k]];
+      en[k] = in[k] ? hist[bk[k] + 1u] : st[k];
+      m = max(m, en[k] - st[k]);
+    }
+    const bool full = m > kBucketMax;
+    const bool again = (NT == 64 ? __ballot(full) != 0ull : __syncthreads_or(full) != 0) && level < 3;
+    if (!again) break;
+    sync();
+    ((uint4*)hist)[t] = make_uint4(0u, 0u, 0u, 0u);
+    ((uint4*)bnd)[t] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    ((uint4*)bnd)[t + NT] = make_uint4(0u, 0u, 0u, 0u);
+    sync();
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (in[k]) { atomicMin(&bnd[bk[k]], K[k]); atomicMax(&bnd[bk[k] + 4u * NT], K[k]); }
+    sync();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (!in[k]) continue;
+      const uint32_t lo = bnd[bk[k]], hi = bnd[bk[k] + 4u * NT], c = en[k] - st[k];
+      const float sc = (float)c * __builtin_amdgcn_rcpf((float)(hi - lo) + 1.0f);
+      bk[k] = st[k] + min((uint32_t)((float)(K[k] - lo) * sc), c - 1u);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (in[k]) list[st[k] + arr[k]] = K[k];
+    place[k] = st[k];
+  }
+  sync();
+  for (uint32_t q = 0; q < m; ++q) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const bool on = st[k] + q < en[k];
+      const uint32_t o = list[on ? st[k] + q : 0u];
+      place[k] += on && o < K[k] ? 1u : 0u;
+    }
+  }
+  sync();
+}
+
+// Cells' start offsets of a row unit (one wave): the cell histogram hist[0
+// .. nc) becomes its exclusive scan, also stored.
+__device__ __forceinline__ void wave_cell_offsets(const Ws& w, uint32_t* hist, uint32_t nc, uint32_t cbase,
+                                                  uint32_t n) {
+  const int lane = lane_id();
+  uint32_t carry = 0;
+  for (uint32_t c0 = 0; c0 < nc; c0 += 64) {
+    const uint32_t c = c0 + lane;
+    const uint32_t v = c < nc ? hist[c] : 0u;
+    const uint32_t inc = wave_incl_scan(v);
+    if (c < nc) { hist[c] = carry + inc - v; w.cell_off[cbase + c] = (uint16_t)(carry + inc - v); }
+    carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+  }
+  if (lane == 0) w.cell_off[cbase + nc] = (uint16_t)n;
+}
+
 // Row units of at most 64 clusters (most units of small events): one wave
 // each, four per workgroup, no workgroup barrier.  Lane k holds the k-th
-// entry: the ids are sorted by a bitonic network over lane shuffles, the
-// coordinates follow by a gather from the lane that held them; the grid is
+// entry: its place is counted over the ids (eight per two LDS reads that
+// every lane shares), the entries change lanes through LDS; the grid is
 // built as in k_rows with a per-wave LDS histogram.  Same results as k_rows.
+// Bound by its instructions.
 __global__ __launch_bounds__(TB) void k_rows_tiny(Ws w) {
-  __shared__ uint32_t s_h[TB / 64][kCellsPerCluster * kTiny + 2];
+  constexpr uint32_t kH = (kCellsPerCluster * kTiny + 2 + 3) & ~3u;
+  __shared__ alignas(16) uint32_t s_h[TB / 64][kH];
+  __shared__ float4 s_rec[TB / 64][kTiny];
   const int wv = threadIdx.x >> 6, lane = lane_id();
   const int64_t ru = (int64_t)blockIdx.x * (TB / 64) + wv;
   if (ru >= w.RU) return;
@@ -517,163 +658,121 @@ __global__ __launch_bounds__(TB) void k_rows_tiny(Ws w) {
   if (n > kTiny) return;
   const uint32_t cbase = w.cell_base[ru];
   uint32_t* hist = s_h[wv];
-  float x0 = 0.f, y0 = 0.f, z0 = 0.f;
-  uint32_t key = 0xFFFFFFFFu, slot = (uint32_t)lane;
-  if ((uint32_t)lane < n) {
-    const float4 v = w.tmp4[off + lane];
-    x0 = v.x; y0 = v.y; z0 = v.z; key = __float_as_uint(v.w);
-  }
-  uint32_t npad = 2;
-  while (npad < n) npad <<= 1;
-  for (uint32_t kk = 2; kk <= npad; kk <<= 1) {
-    for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
-      const uint32_t o = (uint32_t)__shfl_xor((int)key, (int)j, 64);
-      const uint32_t os = (uint32_t)__shfl_xor((int)slot, (int)j, 64);
-      const bool lower = ((uint32_t)lane & j) == 0, asc = ((uint32_t)lane & kk) == 0;
-      const uint32_t lo = lower ? key : o, hi = lower ? o : key;
-      if (asc ? lo > hi : lo < hi) { key = o; slot = os; }
-    }
-  }
-  const float x = __shfl(x0, (int)slot, 64), y = __shfl(y0, (int)slot, 64), z = __shfl(z0, (int)slot, 64);
+  float4* rec = s_rec[wv];
   const bool mine = (uint32_t)lane < n;
-  if (mine) {
-    w.cx[off + lane] = x; w.cy[off + lane] = y; w.cz[off + lane] = z;
-    w.cid[off + lane] = key; w.cru[off + lane] = (uint32_t)ru;
+  float4 v = make_float4(0.f, 0.f, 0.f, __uint_as_float(0xFFFFFFFFu));
+  if (mine) v = w.tmp4[off + lane];
+  const uint32_t key = __float_as_uint(v.w);
+  hist[lane] = key;
+  const float4 box = wave_min4(mine ? v.y : INFINITY, mine ? -v.y : INFINITY, mine ? v.z : INFINITY,
+                               mine ? -v.z : INFINITY);
+  wave_sync();
+  uint32_t place = 0;
+  const uint4* k4 = (const uint4*)hist;
+  for (uint32_t i = 0; i < n; i += 8) {
+    const uint4 a = k4[i >> 2], b = k4[(i >> 2) + 1];
+    place += a.x < key; place += a.y < key; place += a.z < key; place += a.w < key;
+    place += b.x < key; place += b.y < key; place += b.z < key; place += b.w < key;
   }
-  float ymin = mine ? y : INFINITY, ymax = mine ? y : -INFINITY;
-  float zmin = mine ? z : INFINITY, zmax = mine ? z : -INFINITY;
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) {
-    ymin = fminf(ymin, __shfl_xor(ymin, d, 64)); ymax = fmaxf(ymax, __shfl_xor(ymax, d, 64));
-    zmin = fminf(zmin, __shfl_xor(zmin, d, 64)); zmax = fmaxf(zmax, __shfl_xor(zmax, d, 64));
-  }
+  if (mine) rec[place] = v;
+  wave_sync();
   // grid parameters: every lane computes the same values, lane 0 stores them
-  const GridParams G = make_grid(n, cbase, off, ymin, ymax, zmin, zmax);
+  const GridParams G = make_grid(n, cbase, off, box.x, -box.y, box.z, -box.w);
   if (lane == 0) w.grid[ru] = G;
   const uint32_t nc = G.nz() * G.ny();
-  for (uint32_t c = lane; c <= nc; c += 64) hist[c] = 0u;
+  for (uint32_t c = lane; c < nc; c += 64) hist[c] = 0u;
+  if (mine) {
+    v = rec[lane];
+    w.cx[off + lane] = v.x; w.cy[off + lane] = v.y; w.cz[off + lane] = v.z;
+    w.cid[off + lane] = __float_as_uint(v.w); w.cru[off + lane] = (uint32_t)ru;
+  }
   wave_sync();
-  const uint32_t cell = mine ? cell_of(G, y, z) : 0u;
+  const uint32_t cell = mine ? cell_of(G, v.y, v.z) : 0u;
   if (mine) atomicAdd(&hist[cell], 1u);
   wave_sync();
-  uint32_t carry = 0;
-  for (uint32_t c0 = 0; c0 < nc; c0 += 64) {
-    const uint32_t c = c0 + lane;
-    const uint32_t v = c < nc ? hist[c] : 0u;
-    const uint32_t inc = wave_incl_scan(v);
-    if (c < nc) { hist[c] = carry + inc - v; w.cell_off[cbase + c] = (uint16_t)(carry + inc - v); }
-    carry += (uint32_t)__shfl((int)inc, 63, 64);
-  }
-  if (lane == 0) w.cell_off[cbase + nc] = (uint16_t)n;
+  wave_cell_offsets(w, hist, nc, cbase, n);
   wave_sync();
   if (mine) {
     const uint32_t pos = atomicAdd(&hist[cell], 1u);
-    w.gbuf[off + pos] = make_float4(y, z, x, __uint_as_float(off + lane));
+    w.gbuf[off + pos] = make_float4(v.y, v.z, v.x, __uint_as_float(off + lane));
   }
 }
 
 // Row units of kTiny < n <= kWaveRow clusters: one wave each, four per
-// workgroup, no workgroup barrier.  Lane l holds entries 4l .. 4l+3; the
-// bitonic sort on the ids swaps registers for partners in the same lane and
-// uses shuffles otherwise, then every sorted entry's coordinates are read
-// from its original slot; the grid is built with a per-wave LDS histogram.
-// Same results as k_rows.
+// workgroup, no workgroup barrier.  Lane l holds entries l, 64 + l, ..; their
+// places come from id buckets, the entries change lanes through LDS; the
+// grid is built with a per-wave LDS histogram.  Same results as k_rows.
 __global__ __launch_bounds__(TB) void k_rows_wave(Ws w) {
-  __shared__ uint32_t s_h[TB / 64][kCellsPerCluster * kWaveRow + 2];
+  constexpr uint32_t kList = kWaveRow + 4;   // the bucketed ids behind the buckets' bounds
+  constexpr uint32_t kH = kList + kWaveRow;
+  static_assert(kH >= kCellsPerCluster * kWaveRow + 1, "cells");
+  __shared__ alignas(16) uint32_t s_h[TB / 64][kH];
+  __shared__ float4 s_rec[TB / 64][kWaveRow];
   const int wv = threadIdx.x >> 6, lane = lane_id();
   uint32_t* hist = s_h[wv];
+  uint32_t* list = hist + kList;
+  float4* rec = s_rec[wv];
   auto unit = [&](const int64_t ru) {
     const uint32_t off = w.ru_off[ru];
     const uint32_t n = w.ru_off[ru + 1] - off;
     if (rows_class(n) != 1) return;
     const uint32_t cbase = w.cell_base[ru];
-    uint32_t K[4], V[4];
+    float4 v[4];
+    uint32_t K[4];
+    bool in[4];
+    float b0 = INFINITY, b1 = INFINITY, b2 = INFINITY, b3 = INFINITY;
+    uint32_t k0 = 0xFFFFFFFFu, k1 = 0xFFFFFFFFu;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const uint32_t i = 4u * lane + k;
-      K[k] = i < n ? __float_as_uint(w.tmp4[off + i].w) : 0xFFFFFFFFu;
-      V[k] = i;
+      const uint32_t i = (uint32_t)lane + 64u * k;
+      in[k] = i < n;
+      v[k] = w.tmp4[off + (in[k] ? i : 0u)];
     }
-    auto cs = [&](int k0, int k1, uint32_t kk) {   // registers k0 < k1 of this lane
-      const bool asc = ((4u * lane + k0) & kk) == 0;
-      if (asc ? K[k0] > K[k1] : K[k0] < K[k1]) {
-        const uint32_t t = K[k0]; K[k0] = K[k1]; K[k1] = t;
-        const uint32_t u = V[k0]; V[k0] = V[k1]; V[k1] = u;
-      }
-    };
-    uint32_t npad = 2;
-    while (npad < n) npad <<= 1;
-    for (uint32_t kk = 2; kk <= npad; kk <<= 1) {
-      for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
-        if (j == 1) {
-          cs(0, 1, kk); cs(2, 3, kk);
-        } else if (j == 2) {
-          cs(0, 2, kk); cs(1, 3, kk);
-        } else {
-          uint32_t O[4], OV[4];
+    ((uint4*)hist)[lane] = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            O[k] = (uint32_t)__shfl_xor((int)K[k], (int)(j >> 2), 64);
-            OV[k] = (uint32_t)__shfl_xor((int)V[k], (int)(j >> 2), 64);
-          }
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const uint32_t i = 4u * lane + k;
-            const bool lower = (i & j) == 0, asc = (i & kk) == 0;
-            const uint32_t lo = lower ? K[k] : O[k], hi = lower ? O[k] : K[k];
-            if (asc ? lo > hi : lo < hi) { K[k] = O[k]; V[k] = OV[k]; }
-          }
-        }
-      }
+    for (int k = 0; k < 4; ++k) {   // (entries past the end repeat the first)
+      K[k] = __float_as_uint(v[k].w);
+      b0 = fminf(b0, v[k].y); b1 = fminf(b1, -v[k].y); b2 = fminf(b2, v[k].z); b3 = fminf(b3, -v[k].z);
+      k0 = min(k0, K[k]); k1 = min(k1, ~K[k]);
     }
-    float px[4], py[4], pz[4];
-    float ymin = INFINITY, ymax = -INFINITY, zmin = INFINITY, zmax = -INFINITY;
+    const float4 box = wave_min4(b0, b1, b2, b3);
+    const uint2 kr = wave_min2(k0, k1);
+    wave_sync();
+    uint32_t place[4];
+    id_places<64>(K, in, n, kr.x, ~kr.y, hist, list, (uint32_t*)rec, place);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint32_t i = 4u * lane + k;
-      px[k] = py[k] = pz[k] = 0.f;
-      if (i < n) {
-        const float4 v = w.tmp4[off + V[k]];
-        px[k] = v.x; py[k] = v.y; pz[k] = v.z;
-        w.cx[off + i] = v.x; w.cy[off + i] = v.y; w.cz[off + i] = v.z;
-        w.cid[off + i] = K[k]; w.cru[off + i] = (uint32_t)ru;
-        ymin = fminf(ymin, v.y); ymax = fmaxf(ymax, v.y); zmin = fminf(zmin, v.z); zmax = fmaxf(zmax, v.z);
-      }
-    }
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-      ymin = fminf(ymin, __shfl_xor(ymin, d, 64)); ymax = fmaxf(ymax, __shfl_xor(ymax, d, 64));
-      zmin = fminf(zmin, __shfl_xor(zmin, d, 64)); zmax = fmaxf(zmax, __shfl_xor(zmax, d, 64));
-    }
+    for (int k = 0; k < 4; ++k)
+      if (in[k]) rec[place[k]] = v[k];
+    wave_sync();
     // every lane computes the same grid, lane 0 stores it
-    const GridParams G = make_grid(n, cbase, off, ymin, ymax, zmin, zmax);
+    const GridParams G = make_grid(n, cbase, off, box.x, -box.y, box.z, -box.w);
     if (lane == 0) w.grid[ru] = G;
     const uint32_t nc = G.nz() * G.ny();
-    for (uint32_t c = lane; c <= nc; c += 64) hist[c] = 0u;
+    for (uint32_t c = lane; c < nc; c += 64) hist[c] = 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t i = (uint32_t)lane + 64u * k;
+      if (in[k]) {
+        v[k] = rec[i];
+        w.cx[off + i] = v[k].x; w.cy[off + i] = v[k].y; w.cz[off + i] = v[k].z;
+        w.cid[off + i] = __float_as_uint(v[k].w); w.cru[off + i] = (uint32_t)ru;
+      }
+    }
     wave_sync();
     uint32_t cell[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      cell[k] = 4u * lane + k < n ? cell_of(G, py[k], pz[k]) : 0u;
-      if (4u * lane + k < n) atomicAdd(&hist[cell[k]], 1u);
+      cell[k] = in[k] ? cell_of(G, v[k].y, v[k].z) : 0u;
+      if (in[k]) atomicAdd(&hist[cell[k]], 1u);
     }
     wave_sync();
-    uint32_t carry = 0;
-    for (uint32_t c0 = 0; c0 < nc; c0 += 64) {
-      const uint32_t c = c0 + lane;
-      const uint32_t v = c < nc ? hist[c] : 0u;
-      const uint32_t inc = wave_incl_scan(v);
-      if (c < nc) { hist[c] = carry + inc - v; w.cell_off[cbase + c] = (uint16_t)(carry + inc - v); }
-      carry += (uint32_t)__shfl((int)inc, 63, 64);
-    }
-    if (lane == 0) w.cell_off[cbase + nc] = (uint16_t)n;
+    wave_cell_offsets(w, hist, nc, cbase, n);
     wave_sync();
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const uint32_t i = 4u * lane + k;
-      if (i < n) {
+      if (in[k]) {
         const uint32_t pos = atomicAdd(&hist[cell[k]], 1u);
-        w.gbuf[off + pos] = make_float4(py[k], pz[k], px[k], __uint_as_float(off + i));
+        w.gbuf[off + pos] = make_float4(v[k].y, v[k].z, v[k].x, __uint_as_float(off + (uint32_t)lane + 64u * k));
       }
     }
   };
@@ -689,6 +788,11 @@ __global__ __launch_bounds__(TB) void k_rows_wave(Ws w) {
   }
 }
 
+// One workgroup per row unit: the row unit's (x, y, z, id) entries sorted by
+// id, canonical SoA written in that order, then a uniform 2-D grid over the
+// row's bounding box with about kCellsPerCluster cells per cluster, filled by
+// an LDS counting sort.
+//
 // Two instantiations: row units of kWaveRow < n <= 4 TB clusters (small LDS,
 // so many workgroups share a CU) and larger ones (LDS for kMaxRow ids).  With few row
 // units a launch covers every unit and skips those of the other sizes; with
@@ -697,11 +801,15 @@ template <bool kLarge>
 __global__ __launch_bounds__(TB) void k_rows(Ws w) {
   constexpr uint32_t kIds = kLarge ? (uint32_t)kMaxRow : 4u * TB;
   constexpr uint32_t kCells = kLarge ? (uint32_t)kMaxCells : kCellsPerCluster * 4u * TB + 1u;   // grid_cells(n) bound
-  __shared__ uint32_t s_ids[kIds];
-  // slots (16 bit) during the sort, then the cell histogram
-  __shared__ uint32_t s_aux[(kCells + 1) > kIds / 2 ? (kCells + 1) : kIds / 2];
-  __shared__ float s_red[4][TB / 64];
-  __shared__ GridParams s_gp;
+  // large units: the ids being sorted; others: the bucketed ids, then the
+  // entries on their way to the threads of their places
+  __shared__ float4 s_mem[kLarge ? kIds / 4 : kIds];
+  // large units: slots (16 bit) during the sort; others: the bounds of the
+  // id buckets; then the cell histogram
+  __shared__ alignas(16) uint32_t s_aux[(kCells + 1) > kIds / 2 ? (kCells + 1) : kIds / 2];
+  __shared__ float4 s_box[TB / 64];
+  __shared__ uint2 s_key[TB / 64];
+  uint32_t* s_ids = (uint32_t*)s_mem;
   uint16_t* s_slot = (uint16_t*)s_aux;
   uint32_t* s_hist = s_aux;
   // one row unit (workgroup-uniform); called once per unit of the launch
@@ -730,75 +838,57 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
       }
       return;
     }
-    // Rows of up to 4 TB clusters (all but extreme ones) are sorted in
-    // registers: thread t holds sorted positions 4t .. 4t+3; bitonic stages
-    // whose partner is in the same thread swap registers, partners in the
-    // same wave come by shuffles, and only the stages across waves (partner
-    // distance >= 256) go through LDS.  Their coordinates then stay in
-    // registers for the grid passes.
+    // Units of up to 4 TB clusters (all but extreme ones): thread t holds
+    // entries t, TB + t, ..; their places come from id buckets, the entries
+    // change threads through LDS and stay in registers for the grid passes.
     const bool fast = !kLarge;
-    uint32_t K[4], V[4];
-    float px[4], py[4], pz[4];
-    float ymin = INFINITY, ymax = -INFINITY, zmin = INFINITY, zmax = -INFINITY;
+    float4 v[4];
+    bool in[4];
+    float b0 = INFINITY, b1 = INFINITY, b2 = INFINITY, b3 = INFINITY;
+    uint32_t k0 = 0xFFFFFFFFu, k1 = 0xFFFFFFFFu;
+    // the workgroup's minima of the box (all threads); the ids' in k0, k1
+    auto reduce = [&]() {
+      const float4 b = wave_min4(b0, b1, b2, b3);
+      const uint2 kk = wave_min2(k0, k1);
+      if (lane_id() == 0) { s_box[tid >> 6] = b; s_key[tid >> 6] = kk; }
+      __syncthreads();
+  #pragma unroll
+      for (int i = 0; i < TB / 64; ++i) {
+        const float4 o = s_box[i];
+        const uint2 q = s_key[i];
+        b0 = fminf(b0, o.x); b1 = fminf(b1, o.y); b2 = fminf(b2, o.z); b3 = fminf(b3, o.w);
+        k0 = min(k0, q.x); k1 = min(k1, q.y);
+      }
+    };
     if (fast) {
+      uint32_t K[4];
   #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const uint32_t i = 4u * tid + k;
-        K[k] = i < n ? __float_as_uint(w.tmp4[off + i].w) : 0xFFFFFFFFu;
-        V[k] = i;
+        const uint32_t i = (uint32_t)tid + TB * k;
+        in[k] = i < n;
+        v[k] = w.tmp4[off + (in[k] ? i : 0u)];
       }
-      auto cs = [&](int k0, int k1, uint32_t kk) {   // registers k0 < k1 of this thread
-        const bool asc = ((4u * tid + k0) & kk) == 0;
-        if (asc ? K[k0] > K[k1] : K[k0] < K[k1]) {
-          const uint32_t t = K[k0]; K[k0] = K[k1]; K[k1] = t;
-          const uint32_t u = V[k0]; V[k0] = V[k1]; V[k1] = u;
-        }
-      };
-      // stages up to the row's power-of-two size only: the entries past it are
-      // all padding (equal maxima), already in order
-      uint32_t npad = 2;
-      while (npad < n) npad <<= 1;
-      for (uint32_t kk = 2; kk <= npad; kk <<= 1) {
-        for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
-          if (j == 1) {
-            cs(0, 1, kk); cs(2, 3, kk);
-          } else if (j == 2) {
-            cs(0, 2, kk); cs(1, 3, kk);
-          } else {
-            uint32_t O[4], OV[4];
-            if (j < 256) {
+      ((uint4*)s_aux)[tid] = make_uint4(0u, 0u, 0u, 0u);
   #pragma unroll
-              for (int k = 0; k < 4; ++k) {
-                O[k] = (uint32_t)__shfl_xor((int)K[k], (int)(j >> 2), 64);
-                OV[k] = (uint32_t)__shfl_xor((int)V[k], (int)(j >> 2), 64);
-              }
-            } else {
-              __syncthreads();
-  #pragma unroll
-              for (int k = 0; k < 4; ++k) { s_ids[4u * tid + k] = K[k]; s_slot[4u * tid + k] = (uint16_t)V[k]; }
-              __syncthreads();
-  #pragma unroll
-              for (int k = 0; k < 4; ++k) { O[k] = s_ids[(4u * tid + k) ^ j]; OV[k] = s_slot[(4u * tid + k) ^ j]; }
-            }
-  #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const uint32_t i = 4u * tid + k;
-              const bool lower = (i & j) == 0, asc = (i & kk) == 0;
-              const uint32_t lo = lower ? K[k] : O[k], hi = lower ? O[k] : K[k];
-              if (asc ? lo > hi : lo < hi) { K[k] = O[k]; V[k] = OV[k]; }
-            }
-          }
-        }
+      for (int k = 0; k < 4; ++k) {   // (entries past the end repeat the first)
+        K[k] = __float_as_uint(v[k].w);
+        b0 = fminf(b0, v[k].y); b1 = fminf(b1, -v[k].y); b2 = fminf(b2, v[k].z); b3 = fminf(b3, -v[k].z);
+        k0 = min(k0, K[k]); k1 = min(k1, ~K[k]);
       }
+      reduce();
+      uint32_t place[4];
+      id_places<TB>(K, in, n, k0, ~k1, s_aux, s_ids, s_ids + 4 * TB, place);
+  #pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (in[k]) s_mem[place[k]] = v[k];
+      __syncthreads();
   #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const uint32_t i = 4u * tid + k;
-        if (i < n) {
-          const float4 v = w.tmp4[off + V[k]];
-          px[k] = v.x; py[k] = v.y; pz[k] = v.z;
-          w.cx[off + i] = v.x; w.cy[off + i] = v.y; w.cz[off + i] = v.z;
-          w.cid[off + i] = K[k]; w.cru[off + i] = (uint32_t)ru;
-          ymin = fminf(ymin, v.y); ymax = fmaxf(ymax, v.y); zmin = fminf(zmin, v.z); zmax = fmaxf(zmax, v.z);
+        const uint32_t i = (uint32_t)tid + TB * k;
+        if (in[k]) {
+          v[k] = s_mem[i];
+          w.cx[off + i] = v[k].x; w.cy[off + i] = v[k].y; w.cz[off + i] = v[k].z;
+          w.cid[off + i] = __float_as_uint(v[k].w); w.cru[off + i] = (uint32_t)ru;
         }
       }
     } else {
@@ -830,36 +920,19 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
         const float x = v.x, y = v.y, z = v.z;
         w.cx[off + k] = x; w.cy[off + k] = y; w.cz[off + k] = z;
         w.cid[off + k] = s_ids[k]; w.cru[off + k] = (uint32_t)ru;
-        ymin = fminf(ymin, y); ymax = fmaxf(ymax, y); zmin = fminf(zmin, z); zmax = fmaxf(zmax, z);
+        b0 = fminf(b0, y); b1 = fminf(b1, -y); b2 = fminf(b2, z); b3 = fminf(b3, -z);
       }
+      reduce();
     }
-  #pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-      ymin = fminf(ymin, __shfl_xor(ymin, d, 64)); ymax = fmaxf(ymax, __shfl_xor(ymax, d, 64));
-      zmin = fminf(zmin, __shfl_xor(zmin, d, 64)); zmax = fmaxf(zmax, __shfl_xor(zmax, d, 64));
-    }
-    if (lane_id() == 0) {
-      s_red[0][tid >> 6] = ymin; s_red[1][tid >> 6] = ymax; s_red[2][tid >> 6] = zmin; s_red[3][tid >> 6] = zmax;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      for (int i = 1; i < TB / 64; ++i) {
-        ymin = fminf(ymin, s_red[0][i]); ymax = fmaxf(ymax, s_red[1][i]);
-        zmin = fminf(zmin, s_red[2][i]); zmax = fmaxf(zmax, s_red[3][i]);
-      }
-      const GridParams G = make_grid(n, cbase, off, ymin, ymax, zmin, zmax);
-      s_gp = G;
-      w.grid[ru] = G;
-    }
-    __syncthreads();
-    const GridParams G = s_gp;
+    const GridParams G = make_grid(n, cbase, off, b0, -b1, b2, -b3);
+    if (tid == 0) w.grid[ru] = G;
     const uint32_t nc = G.nz() * G.ny();
     for (uint32_t c = tid; c <= nc; c += TB) s_hist[c] = 0u;
     __syncthreads();
     if (fast) {
   #pragma unroll
       for (int k = 0; k < 4; ++k)
-        if (4u * tid + k < n) atomicAdd(&s_hist[cell_of(G, py[k], pz[k])], 1u);
+        if (in[k]) atomicAdd(&s_hist[cell_of(G, v[k].y, v[k].z)], 1u);
     } else {
       // the canonical entries were written by this same thread (same k
       // stride): re-read them, coalesced
@@ -880,10 +953,9 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
     if (fast) {
   #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const uint32_t i = 4u * tid + k;
-        if (i < n) {
-          const uint32_t slot = atomicAdd(&s_hist[cell_of(G, py[k], pz[k])], 1u);
-          w.gbuf[off + slot] = make_float4(py[k], pz[k], px[k], __uint_as_float(off + i));
+        if (in[k]) {
+          const uint32_t slot = atomicAdd(&s_hist[cell_of(G, v[k].y, v[k].z)], 1u);
+          w.gbuf[off + slot] = make_float4(v[k].y, v[k].z, v[k].x, __uint_as_float(off + (uint32_t)tid + TB * k));
         }
       }
     } else {
@@ -1416,15 +1488,6 @@ __global__ __launch_bounds__(TB) void k_start_tap(Ws w) {
 // ----------------------------------------------------------- a5: tracklets
 struct Found { int32_t pos; float y, z, x; };
 
-template <int kCtrl>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xF, 0xF, true);
-}
-template <int kCtrl>
-__device__ __forceinline__ float dpp_f32(float v) { return __uint_as_float(dpp_u32<kCtrl>(__float_as_uint(v))); }
-// Lane exchanges inside groups of two, four and eight lanes (the last one
-// mirrors the eight: enough once each four hold one value).
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppMirror8 = 0x141;
 
 template <int G, class F>
 __device__ __forceinline__ void group_steps(F&& f) {

@@ -469,3 +469,43 @@ def test_batch_in_shared_arrays_equals_events_apart(tracker, dev):
             ta, tb = getattr(a, k), getattr(b, k)
             assert ta.is_contiguous() and torch.equal(ta, tb), (e, k)
             assert ta.numel() == 0 or ta.data_ptr() % 16 == 0, (e, k)
+
+
+@pytest.mark.parametrize("order", ["random", "by_row", "two_clumps", "outlier", "geometric"])
+def test_id_order_of_row_units(tracker, orc, order):
+    """Row units at the edges of the row kernels' sizes, with ids that are
+    spread evenly, follow each other, lie in two clumps, leave one entry far
+    from the others, or thin out geometrically: links, tracklets and tracks
+    of the event, and of the event in a batch (size classes by list), equal
+    the oracle."""
+    import dataclasses
+    ev = synth.make_event(seed=51, n_primaries=100, noise=0.01, single_sector=True)
+    sizes = (1, 2, 8, 9, 63, 64, 65, 66, 128, 200, 255, 256, 257, 300, 511, 700, 1022, 1023, 1024)
+    have = np.bincount(ev.row[ev.sector == 0], minlength=ev.geom.n_rows)
+    patches = [(20 + 5 * i, n - int(have[20 + 5 * i]), (-8.0, 8.0), (30.0, 200.0)) for i, n in enumerate(sizes)]
+    ev = _with_patches(ev, [p for p in patches if p[1] > 0], seed=52)
+    n = ev.n
+    rng = np.random.default_rng(53)
+    perm = rng.permutation(n)
+    by_row = perm[np.argsort(ev.row[perm], kind="stable")]
+    first = np.ones(n, bool)
+    first[1:] = ev.row[by_row][1:] != ev.row[by_row][:-1]
+    if order == "by_row":
+        perm = by_row
+    elif order == "two_clumps":
+        perm = np.concatenate([by_row[::2], by_row[1::2]])
+    elif order == "outlier":
+        perm = np.concatenate([by_row[~first], by_row[first]])
+    elif order == "geometric":
+        rank = np.arange(n) - np.maximum.accumulate(np.where(first, np.arange(n), 0))
+        perm = by_row[np.argsort(np.floor(1.01 ** rank * 4.0), kind="stable")]
+    ev = dataclasses.replace(ev, **{k: getattr(ev, k)[perm] for k in
+                                    ("x", "y", "z", "row", "sector", "x64", "y64", "z64", "truth_track",
+                                     "truth_double")})
+    t = to_dev(ev)
+    ref = orc.track(ev, precision=32)
+    out = tracker.track(*t, taps=True)
+    compare(ev, out, tracker.debug_tracklets(), ref)
+    for b in tracker.track_batch([t] * 3):
+        compare(ev, b, None, ref, check_taps=False)
+    assert out.n_tracks > 0
