@@ -131,10 +131,8 @@ struct Ws {
   uint32_t* ru_big;     // [RU] row units of the large row class
   uint32_t* ru_links;   // [RU] same for the small-slab and slab link classes
   float4* tmp4;         // [N] (x, y, z, event-local id bits), bucketed by row unit
-  // canonical SoA: (event, sector, row, id) order
-  float* cx;
-  float* cy;
-  float* cz;
+  // canonical order: (event, sector, row, id)
+  float4* cpk;          // [N] (x, y, z, id bits, then the cleaned up link): one load per step of a chain or fit
   uint32_t* cid;        // event-local cluster id
   uint32_t* cru;        // row unit
   // grid-ordered copy for window searches: (y, z, x, canonical position)
@@ -144,9 +142,6 @@ struct Ws {
   // links (canonical positions)
   int32_t* up;
   int32_t* dn;
-  int32_t* cup;
-  float4* cpk;          // [N] (x, y, z, cleaned up-link bits): one load per chain step
-  int32_t* cdn;
   uint8_t* flag;        // bit0 start, bit1 seed
   uint32_t* blk_start;  // [nb + 1]
   uint32_t* blk_seed;   // [nb + 1]

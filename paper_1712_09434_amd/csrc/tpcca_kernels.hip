@@ -683,7 +683,7 @@ __global__ __launch_bounds__(TB) void k_rows_tiny(Ws w) {
   for (uint32_t c = lane; c < nc; c += 64) hist[c] = 0u;
   if (mine) {
     v = rec[lane];
-    w.cx[off + lane] = v.x; w.cy[off + lane] = v.y; w.cz[off + lane] = v.z;
+    w.cpk[off + lane] = v;
     w.cid[off + lane] = __float_as_uint(v.w); w.cru[off + lane] = (uint32_t)ru;
   }
   wave_sync();
@@ -754,7 +754,7 @@ __global__ __launch_bounds__(TB) void k_rows_wave(Ws w) {
       const uint32_t i = (uint32_t)lane + 64u * k;
       if (in[k]) {
         v[k] = rec[i];
-        w.cx[off + i] = v[k].x; w.cy[off + i] = v[k].y; w.cz[off + i] = v[k].z;
+        w.cpk[off + i] = v[k];
         w.cid[off + i] = __float_as_uint(v[k].w); w.cru[off + i] = (uint32_t)ru;
       }
     }
@@ -832,7 +832,7 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
       // reported
       const float nan = __int_as_float(0x7fc00000);
       for (uint32_t k = tid; k < n; k += TB) {
-        w.cx[off + k] = nan; w.cy[off + k] = nan; w.cz[off + k] = nan;
+        w.cpk[off + k] = make_float4(nan, nan, nan, 0.0f);
         w.cid[off + k] = 0u; w.cru[off + k] = (uint32_t)ru;
         w.gbuf[off + k] = make_float4(nan, nan, nan, __uint_as_float(off + k));
       }
@@ -887,7 +887,7 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
         const uint32_t i = (uint32_t)tid + TB * k;
         if (in[k]) {
           v[k] = s_mem[i];
-          w.cx[off + i] = v[k].x; w.cy[off + i] = v[k].y; w.cz[off + i] = v[k].z;
+          w.cpk[off + i] = v[k];
           w.cid[off + i] = __float_as_uint(v[k].w); w.cru[off + i] = (uint32_t)ru;
         }
       }
@@ -917,8 +917,8 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
       }
       for (uint32_t k = tid; k < n; k += TB) {
         const float4 v = w.tmp4[off + s_slot[k]];
-        const float x = v.x, y = v.y, z = v.z;
-        w.cx[off + k] = x; w.cy[off + k] = y; w.cz[off + k] = z;
+        const float y = v.y, z = v.z;
+        w.cpk[off + k] = v;
         w.cid[off + k] = s_ids[k]; w.cru[off + k] = (uint32_t)ru;
         b0 = fminf(b0, y); b1 = fminf(b1, -y); b2 = fminf(b2, z); b3 = fminf(b3, -z);
       }
@@ -936,7 +936,10 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
     } else {
       // the canonical entries were written by this same thread (same k
       // stride): re-read them, coalesced
-      for (uint32_t k = tid; k < n; k += TB) atomicAdd(&s_hist[cell_of(G, w.cy[off + k], w.cz[off + k])], 1u);
+      for (uint32_t k = tid; k < n; k += TB) {
+        const float4 c = w.cpk[off + k];
+        atomicAdd(&s_hist[cell_of(G, c.y, c.z)], 1u);
+      }
     }
     __syncthreads();
     uint32_t carry = 0;
@@ -960,9 +963,9 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
       }
     } else {
       for (uint32_t k = tid; k < n; k += TB) {
-        const float x = w.cx[off + k], y = w.cy[off + k], z = w.cz[off + k];
-        const uint32_t slot = atomicAdd(&s_hist[cell_of(G, y, z)], 1u);
-        w.gbuf[off + slot] = make_float4(y, z, x, __uint_as_float(off + k));
+        const float4 c = w.cpk[off + k];
+        const uint32_t slot = atomicAdd(&s_hist[cell_of(G, c.y, c.z)], 1u);
+        w.gbuf[off + slot] = make_float4(c.y, c.z, c.x, __uint_as_float(off + k));
       }
     }
   };
@@ -1384,22 +1387,23 @@ __global__ __launch_bounds__(TB) void k_links(Ws w) {
 // Keep a link only if reciprocated (from the raw arrays).  Start hit: kept up
 // link, no kept down link.  Seed: start hit whose chain reaches
 // min_seed_hits clusters.  Optional taps map positions to cluster ids.
+// Bound by memory: the up link goes into the record that the rows have
+// written (4 bytes of its 16; records written here as well took 55 us
+// instead of 43 on 3.8 M clusters, a link array of its own 36 but 15 more in
+// the tracklets' chains, which then wait for two loads a step).
 __global__ __launch_bounds__(TB) void k_clean(Ws w) {
   __shared__ uint32_t s_cnt[2][TB / 64];
   const int64_t p = (int64_t)blockIdx.x * TB + threadIdx.x;
   bool start = false, seed = false;
   if (p < w.N) {
-    // independent loads first, then both reciprocity gathers together
+    // both links, then both reciprocity gathers together
     // (a missing link reads the cluster's own entry, which is not used)
     const int32_t u = w.up[p], d = w.dn[p];
-    const float x = w.cx[p], y = w.cy[p], z = w.cz[p];
     const int32_t du = w.dn[u >= 0 ? u : (int32_t)p];
     const int32_t ud = w.up[d >= 0 ? d : (int32_t)p];
     const int32_t cu = (u >= 0 && du == (int32_t)p) ? u : -1;
     const int32_t cd = (d >= 0 && ud == (int32_t)p) ? d : -1;
-    w.cup[p] = cu;
-    w.cdn[p] = cd;
-    w.cpk[p] = make_float4(x, y, z, __int_as_float(cu));
+    w.cpk[p].w = __int_as_float(cu);
     start = cu >= 0 && cd < 0;
     if (start) {
       int L = 2;
