@@ -38,6 +38,7 @@ enum : int {
   F_LLINKS2 = 7,
   F_SEEDCTR = 8,    // work counters of the tracklet kernel, one per seed range (8)
   F_LROWS3 = 16,
+  F_LBANDS = 17,    // bands of clusters listed for the ownership kernel's large variant
   F_COUNT = 20
 };
 enum : uint32_t { ERR_INVALID = 1u, ERR_LIMIT = 2u, ERR_STUCK = 4u };

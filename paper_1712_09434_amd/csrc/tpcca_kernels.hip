@@ -1953,20 +1953,34 @@ __global__ __launch_bounds__(TB) void k_tracklets(Ws w) {
 constexpr int kBandRows = 8;
 constexpr int kBandCap = 6144;
 // threads of an ownership workgroup: 1024 where the sectors hold many
-// tracklets (short chains of dependent loads per thread), TB for batches of
-// small events (few tracklets per band, many workgroups)
+// tracklets (short chains of dependent loads per thread), TB for smaller
+// events
 constexpr int TBO = 1024;
 
-__global__ __launch_bounds__(TBO) void k_owner(Ws w) {
-  const uint32_t nt = blockDim.x;   // (TBO for events of many tracklets, TB otherwise)
-  __shared__ unsigned long long s_own[kBandCap];
-  const int nband = (w.R + kBandRows - 1) / kBandRows;
-  const int64_t su = blockIdx.x / nband;
-  const int r_lo = (int)(blockIdx.x % nband) * kBandRows;
-  const int r_hi = min(r_lo + kBandRows, w.R) - 1;
-  const uint32_t c0 = w.ru_off[su * w.R + r_lo], c1 = w.ru_off[su * w.R + r_hi + 1];
-  const uint32_t nc = c1 - c0;
-  const bool lds = nc <= (uint32_t)kBandCap;
+struct Band {
+  int64_t su;        // (event, sector)
+  int r_lo, r_hi;    // rows
+  uint32_t c0, nc;   // canonical positions
+};
+__device__ __forceinline__ Band band_of(const Ws& w, uint32_t b) {
+  const uint32_t nband = (uint32_t)((w.R + kBandRows - 1) / kBandRows);
+  Band d;
+  d.su = b / nband;
+  d.r_lo = (int)(b % nband) * kBandRows;
+  d.r_hi = min(d.r_lo + kBandRows, w.R) - 1;
+  d.c0 = w.ru_off[d.su * w.R + d.r_lo];
+  d.nc = w.ru_off[d.su * w.R + d.r_hi + 1] - d.c0;
+  return d;
+}
+
+// One band by the nt threads of the workgroup; s_own: LDS words for cap
+// clusters.
+__device__ __forceinline__ void own_band(const Ws& w, const Band& d, unsigned long long* s_own, uint32_t cap,
+                                         uint32_t nt) {
+  const int64_t su = d.su;
+  const int r_lo = d.r_lo, r_hi = d.r_hi;
+  const uint32_t c0 = d.c0, nc = d.nc;
+  const bool lds = nc <= cap;
   // every cluster lies in one band, whose workgroup alone takes its
   // maxima: in LDS or, for bands above the LDS capacity, by global atomics
   // on entries this workgroup clears
@@ -2042,6 +2056,38 @@ __global__ __launch_bounds__(TBO) void k_owner(Ws w) {
     }
     mk[s] = (uint8_t)m;
   }
+}
+
+// Every band a workgroup, or the bands that k_owner_small has listed.
+__global__ __launch_bounds__(TBO) void k_owner(Ws w) {
+  __shared__ unsigned long long s_own[kBandCap];
+  if (!ru_lists(w.RU)) {
+    own_band(w, band_of(w, blockIdx.x), s_own, kBandCap, blockDim.x);
+    return;
+  }
+  const uint32_t cnt = w.flags[F_LBANDS];
+  for (uint32_t i = blockIdx.x; i < cnt; i += gridDim.x) {
+    own_band(w, band_of(w, w.ru_big[i]), s_own, kBandCap, blockDim.x);
+    __syncthreads();   // LDS is reused by the next band
+  }
+}
+
+// Batches of events: two waves and 16 KB of LDS per band, so that ten bands
+// share a compute unit (a band of a small event is a chain of four dependent
+// memory trips; workgroups with LDS for the largest bands leave three on a
+// unit: 64 small events 223 -> 96 us).  Larger bands are listed for k_owner,
+// which takes them with TBO threads (24-collision frame: 60 -> 34 and 30).
+constexpr uint32_t kSmallBand = 2048;
+constexpr uint32_t kSmallBandNT = 128;
+__global__ __launch_bounds__(kSmallBandNT) void k_owner_small(Ws w) {
+  __shared__ unsigned long long s_own[kSmallBand];
+  const Band d = band_of(w, blockIdx.x);
+  if (d.nc > kSmallBand) {
+    // (the list of large row units has been used up by the row kernels)
+    if (threadIdx.x == 0) w.ru_big[atomicAdd(&w.flags[F_LBANDS], 1u)] = blockIdx.x;
+    return;
+  }
+  own_band(w, d, s_own, kSmallBand, kSmallBandNT);
 }
 
 // ------------------------------------------------ a6/a7: accept + final fit
@@ -2212,22 +2258,55 @@ __global__ __launch_bounds__(TB) void k_totals(Ws w) {
       w.out[e].hit_off[w.ev_res[e * 4 + 0]] = (int32_t)w.ev_res[e * 4 + 1];
 }
 
-// One wave per accepted tracklet (the ordered accepted list; those whose
-// fit failed are skipped): scalars spread over the lanes, the hit list
-// written in whole cache lines (innermost first).
+// Half a wave per accepted tracklet (the ordered accepted list; those whose
+// fit failed are skipped), two in flight per wave, the tracks of one XCD's
+// range on that XCD (neighbouring tracks share the lines of their clusters'
+// ids).  A lane stores one scalar and every 32nd hit, innermost first.  Bound
+// by a chain of dependent memory trips: everything indexed by the tracklet
+// is read in the first, the hits before their count is known; a wave per
+// tracklet, its hits read after the count, took 154 us, this way 117
+// (64 small events; 3.8 M clusters 47 and 35).
+constexpr unsigned kWriteGrid = 2048;   // workgroups resident at once (a multiple of kXcd)
 __global__ __launch_bounds__(TB) void k_write(Ws w) {
   if (w.flags[F_FITS] == 0u) return;
   const uint32_t na = w.acc_off[w.seed_cap];
-  const int lane = lane_id();
-  const int64_t nw = (int64_t)gridDim.x * (TB / 64);
-  for (int64_t i = (int64_t)blockIdx.x * (TB / 64) + (threadIdx.x >> 6); i < na; i += nw) {
+  const int hl = lane_id() & 31;
+  // the lane's scalar: its value's place in the fit record, its output array
+  // and its place in the track's entry there
+  int rfi = hl, at = 0, per = 1;
+  const auto field = [](size_t o) { return (int)o; };
+  int fo = 0;
+  if (hl < 5) { rfi = 1 + hl; fo = field(offsetof(EventOut, p)); at = hl; per = 5; }
+  else if (hl < 20) { rfi = 1 + hl; fo = field(offsetof(EventOut, cov)); at = hl - 5; per = 15; }
+  else if (hl == 20) { rfi = 0; fo = field(offsetof(EventOut, x_ref)); }
+  else if (hl == 21) fo = field(offsetof(EventOut, chi2));
+  else if (hl == 22) fo = field(offsetof(EventOut, k_prior));
+  else if (hl == 23) fo = field(offsetof(EventOut, ndf));
+  else if (hl == 24) fo = field(offsetof(EventOut, hit_off));
+  else fo = field(offsetof(EventOut, sector));
+  if (hl > 22) rfi = 0;
+  const uint32_t x = blockIdx.x % kXcd;
+  const int64_t lo = (int64_t)(((uint64_t)na * x) / kXcd), hi = (int64_t)(((uint64_t)na * (x + 1)) / kXcd);
+  const int64_t stride = (int64_t)(gridDim.x / kXcd) * (TB / 32);
+  for (int64_t i = lo + (int64_t)(blockIdx.x / kXcd) * (TB / 32) + (threadIdx.x >> 5); i < hi; i += stride) {
     const int64_t s = w.acc_list[i];
-    // everything indexed by s in one round trip
     const uint32_t t0 = w.trk_flag[s], t1 = w.trk_flag[s + 1];
     const uint32_t c0 = w.hit_cnt[s], c1 = w.hit_cnt[s + 1];
     const int32_t h0 = (int32_t)w.seeds[s];
+    const float v = w.rf[s * kRf + rfi];
+    const int32_t* own = w.tl_own + s * w.R;
+    constexpr int kPass = 8;   // (at most 255 rows)
+    int32_t h[kPass];
+#pragma unroll
+    for (int c = 0; c < kPass; ++c)
+      if (32 * c < w.R) h[c] = own[min(hl + 32 * c, w.R - 1)];
     if (t1 == t0) continue;
+    const uint32_t n = c1 - c0;
     const uint32_t vsec = w.cru[h0] / (uint32_t)w.R;
+    uint32_t id[kPass];
+#pragma unroll
+    for (int c = 0; c < kPass; ++c)
+      if ((uint32_t)(hl + 32 * c) < n) id[c] = w.cid[h[c]];
     const int e = (int)(vsec / (uint32_t)w.S);
     const EventOut& O = w.out[e];
     // offsets within the event (a single event starts at zero)
@@ -2237,18 +2316,19 @@ __global__ __launch_bounds__(TB) void k_write(Ws w) {
       j = t0 - w.trk_flag[sb];
       o = c0 - w.hit_cnt[sb];
     }
-    const uint32_t n = c1 - c0;
-    const float* rf = w.rf + s * kRf;
-    if (lane < 5) O.p[j * 5 + lane] = rf[1 + lane];
-    else if (lane < 20) O.cov[j * 15 + (lane - 5)] = rf[6 + (lane - 5)];
-    else if (lane == 20) O.x_ref[j] = rf[0];
-    else if (lane == 21) O.chi2[j] = rf[21];
-    else if (lane == 22) { if (O.k_prior) O.k_prior[j] = rf[22]; }
-    else if (lane == 23) O.sector[j] = (uint8_t)(vsec % (uint32_t)w.S);
-    else if (lane == 24) O.ndf[j] = 2 * (int32_t)n - 5;
-    else if (lane == 25) O.hit_off[j] = (int32_t)o;
-    const int32_t* own = w.tl_own + s * w.R;
-    for (uint32_t q = lane; q < n; q += 64) O.hit_id[o + q] = w.cid[own[n - 1 - q]];
+    char* out = *(char* const*)((const char*)&O + fo);
+    uint32_t* hid = O.hit_id;
+    if (hl < 25) {
+      const uint32_t b = hl < 23 ? __float_as_uint(v) : hl == 23 ? 2u * n - 5u : o;
+      if (out) ((uint32_t*)out)[(int64_t)j * per + at] = b;
+    } else if (hl == 25) {
+      ((uint8_t*)out)[j] = (uint8_t)(vsec % (uint32_t)w.S);
+    }
+#pragma unroll
+    for (int c = 0; c < kPass; ++c) {
+      const uint32_t q = (uint32_t)(hl + 32 * c);
+      if (q < n) hid[o + (n - 1u - q)] = id[c];
+    }
   }
 }
 
@@ -2347,8 +2427,10 @@ hipError_t run_pipeline(const Ws& w, hipStream_t st, const PhaseEvents* pe) {
   k_tracklets<<<tracklet_grid(w), TB, 0, st>>>(w);
   TPCCA_CHECK(hipGetLastError());
   TPCCA_MARK(PH_OWNER);
-  k_owner<<<(unsigned)((int64_t)w.E * w.S * ((w.R + kBandRows - 1) / kBandRows)),
-             w.N / std::max(w.E, 1) >= ((int64_t)1 << 20) ? TBO : TB, 0, st>>>(w);
+  const unsigned nbands = (unsigned)((int64_t)w.E * w.S * ((w.R + kBandRows - 1) / kBandRows));
+  if (lists) k_owner_small<<<nbands, kSmallBandNT, 0, st>>>(w);
+  k_owner<<<lists ? std::min(nbands, kListGrid) : nbands,
+            lists || w.N / std::max(w.E, 1) >= ((int64_t)1 << 20) ? TBO : TB, 0, st>>>(w);
   TPCCA_MARK(PH_REFIT);
   k_accept<<<xcd_blocks(w.seed_cap * 32), TB, 0, st>>>(w);
   TPCCA_CHECK(scan_u32(w.acc_flag, w.acc_off, w.seed_cap, w.scan_tmp, st));
@@ -2359,7 +2441,7 @@ hipError_t run_pipeline(const Ws& w, hipStream_t st, const PhaseEvents* pe) {
   // count) from the owned counts, by the same launches
   TPCCA_CHECK(scan_u32x2(w.own_cnt, w.trk_flag, w.own_cnt, w.hit_cnt, w.seed_cap, w.scan_tmp, st, 1));
   k_totals<<<1, TB, 0, st>>>(w);
-  k_write<<<blocks_for(w.seed_cap * 16, 1 << 13), TB, 0, st>>>(w);
+  k_write<<<std::min(xcd_blocks(w.seed_cap * 32), kWriteGrid), TB, 0, st>>>(w);
   TPCCA_CHECK(hipGetLastError());
   TPCCA_MARK(PH_N);
 #undef TPCCA_MARK

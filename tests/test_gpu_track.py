@@ -509,3 +509,22 @@ def test_id_order_of_row_units(tracker, orc, order):
     for b in tracker.track_batch([t] * 3):
         compare(ev, b, None, ref, check_taps=False)
     assert out.n_tracks > 0
+
+
+def test_batch_with_bands_above_the_small_ownership_class(tracker, orc):
+    """In a batch, bands of up to 2,048 clusters and larger ones (also above
+    the LDS capacity of 6,144) are owned by different kernels: bands at both
+    edges match the oracle, whatever the other events of the batch hold."""
+    ev = synth.make_event(seed=61, n_primaries=150, noise=0.0, single_sector=True)
+    rows = np.bincount(ev.row, minlength=ev.geom.n_rows)
+    patches = []
+    for band, total in ((3, 2047), (5, 2048), (7, 2049), (9, 6144), (11, 6145)):
+        r = range(8 * band, 8 * band + 8)
+        extra = total - int(rows[8 * band:8 * band + 8].sum())
+        patches += [(q, extra // 8 + (1 if k < extra % 8 else 0), (-9.0, 9.0), (30.0, 240.0)) for k, q in enumerate(r)]
+    big = _with_patches(ev, patches, seed=62)
+    small = synth.make_event(seed=63, n_primaries=40, noise=0.02, single_sector=True)
+    print(f"[gpu] bands n={big.n}", flush=True)
+    for ev, out in zip((big, small, big, small), tracker.track_batch([to_dev(e) for e in (big, small, big, small)])):
+        compare(ev, out, None, orc.track(ev, precision=32), check_taps=False)
+        assert out.n_tracks > 0
