@@ -34,8 +34,7 @@ enum : int {
   F_FITS = 3,       // 1 if every event's outputs fit their capacities
   F_LROWS1 = 4,     // list lengths of the row-unit size classes (many row units only):
   F_LROWS2 = 5,     //   row kernels' wave, workgroup and large classes (also F_LROWS3),
-  F_LLINKS1 = 6,    //   link kernels' small-slab and slab classes
-  F_LLINKS2 = 7,
+  F_LLINKS = 6,     // rows listed for the link kernel's large variant
   F_SEEDCTR = 8,    // work counters of the tracklet kernel, one per seed range (8)
   F_LROWS3 = 16,
   F_LBANDS = 17,    // bands of clusters listed for the ownership kernel's large variant
@@ -130,7 +129,7 @@ struct Ws {
   GridParams* grid;     // [RU]
   uint32_t* ru_rows;    // [RU] row units of the wave row class from the front, workgroup class from the back
   uint32_t* ru_big;     // [RU] row units of the large row class
-  uint32_t* ru_links;   // [RU] same for the small-slab and slab link classes
+  uint32_t* ru_links;   // [RU] rows listed for the link kernel's large variant
   float4* tmp4;         // [N] (x, y, z, event-local id bits), bucketed by row unit
   // canonical order: (event, sector, row, id)
   float4* cpk;          // [N] (x, y, z, id bits, then the cleaned up link): one load per step of a chain or fit

@@ -112,19 +112,11 @@ constexpr int64_t kScanSmall = 4 * 4 * kScanNT;      // at most four tiles of 4 
 // each cost a workgroup launch in every variant.
 constexpr uint32_t kTiny = 64;         // clusters of a row unit handled by one wave, one per lane
 constexpr uint32_t kWaveRow = 256;     // clusters of a row unit handled by one wave, four per lane
-constexpr uint32_t kSmallSlab = 256;   // neighbour rows staged in the small-LDS link variant
 constexpr uint32_t kSlab = 896;        // clusters of one row staged in LDS (3 workgroups per CU fit)
 __host__ __device__ inline bool ru_lists(int64_t RU) { return RU > kScanSmall; }
 // 0: k_rows_tiny (empty units too), 1: k_rows_wave, 2: k_rows<false>, 3: k_rows<true>
 __device__ __forceinline__ int rows_class(uint32_t n) {
   return n <= kTiny ? 0 : n <= kWaveRow ? 1 : n <= 4u * TB ? 2 : 3;
-}
-// -1: nothing to do (empty), 0/1/2: k_links<kTiny>, <kSmallSlab>, <kSlab>
-// (the last also writes the no-link entries of edge rows and over-full units)
-__device__ __forceinline__ int links_class(uint32_t n, uint32_t nd, uint32_t nu, bool inner) {
-  if (n == 0) return -1;
-  if (!inner || n > (uint32_t)kMaxRow) return 2;
-  return (nd <= kTiny && nu <= kTiny) ? 0 : (nd <= kSmallSlab && nu <= kSmallSlab) ? 1 : 2;
 }
 // Workgroups of a list-driven launch (each loops over list entries).
 constexpr unsigned kListGrid = 2048, kListGridBig = 1024;
@@ -394,7 +386,7 @@ __device__ __forceinline__ void list_push(bool p, uint32_t v, uint32_t* ctr, uin
 }
 
 // cells + 1 offsets per row unit; with many row units also the lists of the
-// row and link variants (from the counts, before they are reused as cursors)
+// row variants (from the counts, before they are reused as cursors)
 __global__ void k_cell_caps(Ws w) {
   const bool lists = ru_lists(w.RU);
   for (int64_t b0 = (int64_t)blockIdx.x * TB; b0 < w.RU; b0 += (int64_t)gridDim.x * TB) {
@@ -403,15 +395,10 @@ __global__ void k_cell_caps(Ws w) {
     const uint32_t n = ok ? w.ru_count[ru] : 0u;
     if (ok) w.cell_cap[ru] = grid_cells(n) + 1u;
     if (!lists) continue;
-    const int r = ok ? (int)(ru % w.R) : 0;
-    const bool inner = r >= 1 && r <= w.R - 2;
-    const uint32_t nd = ok && inner ? w.ru_count[ru - 1] : 0u, nu = ok && inner ? w.ru_count[ru + 1] : 0u;
-    const int rc = rows_class(n), lc = links_class(n, nd, nu, inner);
+    const int rc = rows_class(n);
     list_push(ok && rc == 1, (uint32_t)ru, &w.flags[F_LROWS1], w.ru_rows, false, w.RU);
     list_push(ok && rc == 2, (uint32_t)ru, &w.flags[F_LROWS2], w.ru_rows, true, w.RU);
     list_push(ok && rc == 3, (uint32_t)ru, &w.flags[F_LROWS3], w.ru_big, false, w.RU);
-    list_push(ok && lc == 1, (uint32_t)ru, &w.flags[F_LLINKS1], w.ru_links, false, w.RU);
-    list_push(ok && lc == 2, (uint32_t)ru, &w.flags[F_LLINKS2], w.ru_links, true, w.RU);
   }
 }
 
@@ -1041,72 +1028,127 @@ __device__ __forceinline__ void find_pair(const Ws& w, float xi, float yi, float
 
 constexpr int kCand = 15;          // passing candidates per side kept per lane
 
+// Candidates of a lane in the band kernel: up to kBandCand entry indexes of 8
+// bits, written to LDS one by one and read back at once.
+constexpr int kBandCand = 16;
+constexpr uint32_t kBandRow = 256;   // entries of a row with such candidates, at most
+struct CandList {
+  uint64_t lo, hi;
+  __device__ __forceinline__ explicit CandList(const uint4& v)
+      : lo(((uint64_t)v.y << 32) | v.x), hi(((uint64_t)v.w << 32) | v.z) {}
+  __device__ __forceinline__ uint32_t pop() {
+    const uint32_t k = (uint32_t)lo & 0xFFu;
+    lo = (lo >> 8) | (hi << 56);
+    hi >>= 8;
+    return k;
+  }
+};
+
 // Window scan of one row's box: indices (into D4) of the entries within the
-// windows, at most kCand; returns the count, or kCand + 1 on overflow.
-template <class F4, class U32>
-__device__ __forceinline__ int collect(const GridParams& G, F4 D4, U32 Dc, float yi, float zi, float WY,
-                                       float WZ, uint16_t* out) {
-  const CellBox b = cell_box(G, yi, zi, WY, WZ);
+// windows, the first kMax of them to out; returns their count.  Two z rows
+// of the box at a time are taken as one list, so that a lane waits for LDS
+// once for their bounds and once per four entries.  The box is taken in
+// cells, with 2e-3 cells for the rounding there (coordinates of at most 4097
+// cells).
+template <int kMax, class Idx>
+__device__ __forceinline__ int collect(const GridParams& G, const float4* D4, const uint16_t* Dc, float yi, float zi,
+                                       float WY, float WZ, Idx* out) {
+  const uint32_t nz = G.nz(), ny = G.ny();
+  const float fz = (float)(nz - 1u), fy = (float)(ny - 1u);
+  const float tz = (zi - G.z0) * G.inv_bz, hz = fmaf(WZ, G.inv_bz, 2e-3f);
+  const float ty = (yi - G.y0) * G.inv_by, hy = fmaf(WY, G.inv_by, 2e-3f);
+  const uint32_t iz0 = (uint32_t)fminf(fmaxf(tz - hz, 0.0f), fz), iz1 = (uint32_t)fminf(fmaxf(tz + hz, 0.0f), fz);
+  const uint32_t iy0 = (uint32_t)fminf(fmaxf(ty - hy, 0.0f), fy), iy1 = (uint32_t)fminf(fmaxf(ty + hy, 0.0f), fy) + 1u;
   int n = 0;
-  for (uint32_t iz = b.iz0; iz <= b.iz1; ++iz) {
-    const uint32_t c0 = iz * G.ny();
-    const uint32_t k0 = Dc[c0 + b.iy0], k1 = Dc[c0 + b.iy1 + 1];
-    // four entries read before any is tested
-    for (uint32_t k = k0; k < k1; k += 4) {
+  for (uint32_t iz = iz0; iz <= iz1; iz += 2) {
+    const uint16_t* c0 = Dc + iz * ny;
+    const uint16_t* c1 = iz < iz1 ? c0 + ny : c0;
+    const uint32_t a0 = c0[iy0], a1 = c0[iy1], e0 = c1[iy0], e1 = c1[iy1];
+    const uint32_t la = a1 - a0, tot = la + (iz < iz1 ? e1 - e0 : 0u), eo = e0 - la;
+    for (uint32_t t = 0; t < tot; t += 4) {
       float4 D[4];
-#pragma unroll
-      for (uint32_t j = 0; j < 4; ++j)
-        if (k + j < k1) D[j] = D4[k + j];
+      uint32_t k[4];
 #pragma unroll
       for (uint32_t j = 0; j < 4; ++j) {
-        if (k + j < k1 && fabsf(D[j].x - yi) <= WY && fabsf(D[j].y - zi) <= WZ) {
-          if (n < kCand) out[n] = (uint16_t)(k + j);
+        const uint32_t u = min(t + j, tot - 1u);
+        k[j] = u + (u < la ? a0 : eo);
+        D[j] = D4[k[j]];
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) {
+        if (t + j < tot && fabsf(D[j].x - yi) <= WY && fabsf(D[j].y - zi) <= WZ) {
+          out[min(n, kMax - 1)] = (Idx)k[j];
           ++n;
         }
       }
     }
   }
-  return n <= kCand ? n : kCand + 1;
+  return n;
 }
 
-// Pairs of one lane's two candidate lists, same arithmetic and tie-break as
-// find_pair (the one-wave and small-slab variants; every pair reads its up
-// candidate from LDS).  The interpolation weight depends only on the two x
-// coordinates, so the quotient of the previous pair is reused when they
-// repeat (clusters on their row planes).
-template <class F4>
-__device__ __forceinline__ void best_pair(const Ws& w, float xi, float yi, float zi, F4 D4, const uint16_t* ld,
-                                          int nd, F4 U4, const uint16_t* lu, int nu, int32_t& bu,
-                                          int32_t& bd) {
-  const float IWY = w.P.inv_var_y, IWZ = w.P.inv_var_z, CUT = w.P.link_cut;
+// Pairs of one lane's candidates (at most kBandCand a side), same arithmetic
+// and tie-break as find_pair.  The least key (score bits, up offset, down
+// offset) is find_pair's choice: a score that passes the cut is >= 0, so its
+// bits order like its value, and the offsets of the rows' canonical
+// positions (fewer than 2^16 entries) order like the positions.  The first
+// four up candidates are read together and kept, the next down candidate is
+// read ahead.  The interpolation weight depends only on the x coordinates:
+// where those of the up candidates agree (clusters on their row planes) its
+// quotient is taken once per x of the down candidates.
+__device__ __forceinline__ void best_pair(const Ws& w, float xi, float yi, float zi, const float4* D4, CandList ld,
+                                          int nd, uint32_t offd, const float4* U4, CandList lu, int nu, uint32_t offu,
+                                          int32_t& bu, int32_t& bd) {
+  const float IWY = w.P.inv_var_y, IWZ = w.P.inv_var_z;
   bu = -1; bd = -1;
   if (nu == 0) return;
-  // (bs, bu, bd) starts at (CUT, INT32_MAX, INT32_MAX): the first pair with
-  // score <= CUT replaces it, later ones must beat the best so far (a NaN
-  // score fails every comparison)
-  float bs = CUT;
-  int32_t ku = INT32_MAX, kd = INT32_MAX;
-  auto take = [&](float score, int32_t pu, int32_t pd) {
-    if (score < bs || (score == bs && (pu < ku || (pu == ku && pd < kd)))) { bs = score; ku = pu; kd = pd; }
+  // (just above every key that passes the cut)
+  const uint64_t none = ((uint64_t)__float_as_uint(w.P.link_cut) << 32) | 0xFFFFFFFFull;
+  uint64_t best = none;
+  constexpr int kKeep = 4;
+  float4 U[kKeep];
+  uint32_t ku[kKeep];
+  bool plane = nu <= kKeep;
+#pragma unroll
+  for (int t = 0; t < kKeep; ++t) {
+    const uint32_t k = lu.pop();
+    U[t] = U4[t < nu ? k : 0u];
+    ku[t] = (__float_as_uint(U[t].w) - offu) << 16;
+    plane = plane && (t >= nu || U[t].z == U[0].z);
+  }
+  auto pair = [&](const float4& D, const float4& Ut, uint32_t low, float wq) {
+    const float ey = yi - fmaf(Ut.x - D.x, wq, D.x);
+    const float ez = zi - fmaf(Ut.y - D.y, wq, D.y);
+    const float score = fmaf(ez * ez, IWZ, (ey * ey) * IWY);
+    const uint64_t key = ((uint64_t)__float_as_uint(score) << 32) | low;
+    best = key < best ? key : best;
   };
-  // the last quotient and the x coordinates it was taken for
-  float wx_d = 0.0f, wx_u = 0.0f, wq = 0.0f;
-  bool wk = false;
+  float4 Dn = D4[ld.pop()];
+  float wx = 0.0f, wq = 0.0f;
   for (int i = 0; i < nd; ++i) {
-    const float4 D = D4[ld[i]];
-    const int32_t pd = (int32_t)__float_as_uint(D.w);
-    for (int j = 0; j < nu; ++j) {
-      const float4 U = U4[lu[j]];
-      if (!(wk && D.z == wx_d && U.z == wx_u)) {
-        wq = (xi - D.z) / (U.z - D.z);
-        wx_d = D.z; wx_u = U.z; wk = true;
+    const float4 D = Dn;
+    const uint32_t k = ld.pop();
+    Dn = D4[i + 1 < nd ? k : 0u];   // (past the last one: not used)
+    const uint32_t kd = __float_as_uint(D.w) - offd;
+    if (plane) {
+      if (i == 0 || D.z != wx) { wq = (xi - D.z) / (U[0].z - D.z); wx = D.z; }
+#pragma unroll
+      for (int t = 0; t < kKeep; ++t)
+        if (t < nu) pair(D, U[t], ku[t] | kd, wq);
+    } else {
+#pragma unroll
+      for (int t = 0; t < kKeep; ++t)
+        if (t < nu) pair(D, U[t], ku[t] | kd, (xi - D.z) / (U[t].z - D.z));
+      CandList rest = lu;
+      for (int j = kKeep; j < nu; ++j) {
+        const float4 Uj = U4[rest.pop()];
+        pair(D, Uj, ((__float_as_uint(Uj.w) - offu) << 16) | kd, (xi - D.z) / (Uj.z - D.z));
       }
-      const float ey = yi - fmaf(U.x - D.x, wq, D.x);
-      const float ez = zi - fmaf(U.y - D.y, wq, D.y);
-      take(fmaf(ez * ez, IWZ, (ey * ey) * IWY), (int32_t)__float_as_uint(U.w), pd);
     }
   }
-  if (ku != INT32_MAX) { bu = ku; bd = kd; }
+  if (best != none) {
+    bu = (int32_t)(offu + ((uint32_t)best >> 16));
+    bd = (int32_t)(offd + ((uint32_t)best & 0xFFFFu));
+  }
 }
 
 // The pairs of a wave's lanes scored by all 64 lanes, same arithmetic and
@@ -1212,40 +1254,157 @@ __device__ __forceinline__ void wave_pairs(const Ws& w, bool has, float xi, floa
   }
 }
 
-// One block per row unit: the grids of rows r-1 and r+1 (entries and cell
-// offsets) are staged in LDS when each holds at most kSlab clusters.  Lanes
-// take the row's clusters in grid (cell) order, so the lanes of a wave are
-// spatial neighbours with similar candidate counts.  A lane first collects
-// the down and up candidates inside the windows (two flat scans), then the
-// pairs are scored: by the lane itself in the two smaller variants, by all
-// lanes of the wave in the slab variant (wave_pairs); nested scanning would
-// make a wave run the product of its lanes' largest candidate counts.
-// Results do not depend on the order.
-//
-// Three instantiations by the size of the neighbour rows: up to kTiny
-// clusters (one wave per row unit, four per workgroup, wave-level ordering),
-// up to kSmallSlab (workgroup per row unit, half the LDS) and the rest
-// (896-cluster slab).  With few row units each launch covers every unit and
-// skips those of the other kinds; with many the two workgroup variants loop
-// over their class's list.
-template <uint32_t kS, uint32_t kG>
-__global__ __launch_bounds__(TB) void k_links(Ws w) {
-  constexpr uint32_t kNG = TB / kG;   // row units per workgroup
-  constexpr int kClass = kS == kTiny ? 0 : kS == kSmallSlab ? 1 : 2;
+// Links of a band of rows of one (event, sector): the grids of the rows and
+// of the two beside them (entries and cell offsets, each one contiguous
+// range) are staged in LDS and the rows' clusters taken in grid order, one
+// per lane, without regard to where a row ends.  A lane first collects the
+// down and up candidates inside the windows (two flat scans), then scores
+// the pairs; nested scanning would make a wave run the product of its lanes'
+// largest candidate counts.  Where the band does not fit, the workgroup
+// takes as many of its rows at a time as fit; a row that does not fit with
+// its neighbours alone is left to k_links.  Results do not depend on the
+// order.  Bound by its instructions: a wave or workgroup per row left half
+// the lanes idle on rows of 33 clusters and staged every row twice (64 small
+// events 583 us, this way 319; 0.77 M clusters 44 and 37).
+constexpr int kLinkRows = 8;             // rows of a band, at most
+// Entries staged, at most and at least (five and six workgroups share a
+// compute unit's LDS).
+constexpr uint32_t kLinkE = 1152, kLinkEMin = 768;
+// 32-bit words of the cell offsets of up to e entries (pairs of 16-bit
+// offsets, aligned as in memory)
+__host__ __device__ inline uint32_t link_words(uint32_t e) { return (kCellsPerCluster * e + 2u * (kLinkRows + 2)) / 2 + 1; }
+
+__global__ __launch_bounds__(TB) void k_links_band(Ws w, int rows, uint32_t cap) {
+  extern __shared__ float4 s_e[];   // cap entries, then the words of their cell offsets
+  uint32_t* s_c = (uint32_t*)(s_e + cap);
+  __shared__ float4 s_g[2 * (kLinkRows + 2)];
+  __shared__ uint32_t s_off[kLinkRows + 3], s_cb[kLinkRows + 3];
+  __shared__ uint4 s_ld[TB], s_lu[TB];
+  const int nband = (w.R + rows - 1) / rows;
+  const int64_t ru0 = (int64_t)(blockIdx.x / nband) * w.R;
+  const int r_lo = (int)(blockIdx.x % nband) * rows, r_hi = min(r_lo + rows, w.R) - 1;
+  const int first = max(r_lo - 1, 0), last = min(r_hi + 1, w.R - 1);   // rows read
+  const int tid = threadIdx.x;
+  if (tid <= last + 1 - first) {
+    s_off[tid] = w.ru_off[ru0 + first + tid];
+    s_cb[tid] = w.cell_base[ru0 + first + tid];
+  }
+  __syncthreads();
+  auto off = [&](int r) { return s_off[r - first]; };
+  // entries of rows r .. r + m - 1 and the two beside them
+  auto need = [&](int r, int m) { return off(min(r + m, w.R - 1) + 1) - off(max(r - 1, 0)); };
+  // a row for k_links
+  auto is_over = [&](int r) {
+    return need(r, 1) > cap || off(r) - off(max(r - 1, 0)) > kBandRow ||
+           off(min(r + 1, w.R - 1) + 1) - off(r + 1) > kBandRow;
+  };
+  if (tid < 64) {
+    const int r = min(r_lo + tid, r_hi);
+    const bool over = r_lo + tid <= r_hi && off(r + 1) > off(r) && is_over(r);
+    if (ru_lists(w.RU)) list_push(over, (uint32_t)(ru0 + r), &w.flags[F_LLINKS], w.ru_links, false, w.RU);
+    else if (over) w.flags[F_LLINKS] = 1u;   // (thousands of additions to one counter would take 35 us)
+  }
+  const float WY = w.P.win_y, WZ = w.P.win_z;
+  for (int r = r_lo; r <= r_hi;) {   // (uniform)
+    const int a = max(r - 1, 0);
+    // the most rows that fit (the lanes try all)
+    const int l = lane_id();
+    const int q = min(r + l, r_hi);
+    const uint64_t ov = __ballot(l > r_hi - r || is_over(q)), fit = __ballot(need(r, q - r + 1) <= cap);
+    const int m = min(__popcll(fit), __ffsll((unsigned long long)ov) - 1);
+    if (m == 0) { ++r; continue; }   // (k_links)
+    const int z = min(r + m, w.R - 1) + 1;   // rows a .. z - 1 are staged
+    const uint32_t o0 = off(a), o1 = off(z), f0 = off(r), f1 = off(r + m);
+    const uint32_t c0 = s_cb[a - first] & ~1u, c1 = s_cb[z - first];
+    if (f1 > f0) {
+      // kLinkEMin entries and their cell offsets per pass, the loads of a
+      // pass issued before its first LDS store (indexes past the end load
+      // the first entry)
+      constexpr int kE = (int)(kLinkEMin / TB), kC = (int)((kCellsPerCluster * kLinkEMin / 2 + kLinkRows + 3 + TB - 1) / TB);
+      const uint32_t* cells = (const uint32_t*)(w.cell_off + c0);
+      const float4* ent = w.gbuf + o0;
+      const uint32_t nc2 = (c1 - c0 + 1u) >> 1, ne = o1 - o0;
+      if (tid < 2 * (z - a)) s_g[tid] = ((const float4*)(w.grid + ru0 + a))[tid];
+      for (uint32_t b0 = 0, d0 = 0; b0 < ne || d0 < nc2; b0 += kE * TB, d0 += kC * TB) {
+        float4 ve[kE];
+        uint32_t vc[kC];
+  #pragma unroll
+        for (int j = 0; j < kE; ++j) {
+          const uint32_t i = b0 + (uint32_t)tid + TB * j;
+          ve[j] = ent[i < ne ? i : 0u];
+        }
+  #pragma unroll
+        for (int j = 0; j < kC; ++j) {
+          const uint32_t i = d0 + (uint32_t)tid + TB * j;
+          vc[j] = cells[i < nc2 ? i : 0u];
+        }
+  #pragma unroll
+        for (int j = 0; j < kE; ++j) {
+          const uint32_t i = b0 + (uint32_t)tid + TB * j;
+          if (i < ne) s_e[i] = ve[j];
+        }
+  #pragma unroll
+        for (int j = 0; j < kC; ++j) {
+          const uint32_t i = d0 + (uint32_t)tid + TB * j;
+          if (i < nc2) s_c[i] = vc[j];
+        }
+      }
+      __syncthreads();
+      const GridParams* g = (const GridParams*)s_g;
+      const uint16_t* cell = (const uint16_t*)s_c;
+      // lane k: where the k-th of the staged rows begins
+      const uint32_t start = l < z - a ? off(a + min(l, z - a)) - o0 : ~0u;
+      for (uint32_t i = f0 - o0 + (uint32_t)tid; i < f1 - o0; i += TB) {
+        const float4 me = s_e[i];
+        // the cluster's row: the last one that begins at or before it (rows
+        // without clusters begin with the one behind them)
+        int q = -1;
+  #pragma unroll
+        for (int k = 0; k < kLinkRows + 2; ++k) q += (uint32_t)__builtin_amdgcn_readlane((int)start, k) <= i ? 1 : 0;
+        const uint32_t p = __float_as_uint(me.w);
+        int32_t bu = -1, bd = -1;
+        if (a + q >= 1 && a + q <= w.R - 2) {   // (edge rows have no links)
+          const float xi = me.z, yi = me.x, zi = me.y;
+          const GridParams Gd = g[q - 1], Gu = g[q + 1];
+          const float4* de = s_e + (Gd.base - o0);
+          const float4* ue = s_e + (Gu.base - o0);
+          const uint16_t* dc = cell + (Gd.cell_base - c0);
+          const uint16_t* uc = cell + (Gu.cell_base - c0);
+          const int cd = collect<kBandCand>(Gd, de, dc, yi, zi, WY, WZ, (uint8_t*)&s_ld[tid]);
+          const int cu = cd > 0 ? collect<kBandCand>(Gu, ue, uc, yi, zi, WY, WZ, (uint8_t*)&s_lu[tid]) : 0;
+          if (cd <= kBandCand && cu <= kBandCand)
+            best_pair(w, xi, yi, zi, de, CandList(s_ld[tid]), cd, Gd.base, ue, CandList(s_lu[tid]), cu, Gu.base, bu, bd);
+          else find_pair(w, xi, yi, zi, Gd, de, dc, Gu, ue, uc, bu, bd);
+        }
+        w.up[p] = bu;
+        w.dn[p] = bd;
+      }
+      __syncthreads();   // LDS is reused by the next rows
+    }
+    r += m;
+  }
+}
+
+// Rows too large for k_links_band, one workgroup each (with many row units
+// from its list): the
+// grids of rows r-1 and r+1 are staged in LDS when each holds at most kSlab
+// clusters.  Lanes take the row's clusters in grid order, so the lanes of a
+// wave are spatial neighbours with similar candidate counts; a wave's pairs
+// are scored by all its lanes (wave_pairs).
+__global__ __launch_bounds__(TB) void k_links(Ws w, uint32_t cap) {
   // one spare slot at the end of each array takes the staging stores of
   // slots past a row's end (never read)
-  constexpr uint32_t kSpareE = kS, kSpareC = kCellsPerCluster * kS + 2;
-  __shared__ float4 s_d[kNG][kS + 1], s_u[kNG][kS + 1];
-  // cell offsets relative to the slab (< kS): 16 bit; a row of <= kS
-  // clusters has at most kCellsPerCluster kS + 1 cells
-  __shared__ uint16_t s_cd[kNG][kSpareC + 1], s_cu[kNG][kSpareC + 1];
+  constexpr uint32_t kSpareE = kSlab, kSpareC = kCellsPerCluster * kSlab + 2;
+  __shared__ float4 sd[kSlab + 1], su[kSlab + 1];
+  // cell offsets relative to the slab (< kSlab): 16 bit; a row of <= kSlab
+  // clusters has at most kCellsPerCluster kSlab + 1 cells
+  __shared__ uint16_t scd[kSpareC + 1], scu[kSpareC + 1];
   __shared__ uint16_t s_ld[kCand * TB], s_lu[kCand * TB];
-  // per-lane best pair keys of the wave-level pair scoring (slab variant)
-  __shared__ unsigned long long s_key[kClass == 2 ? TB : 1];
-  const uint32_t g = threadIdx.x / kG, gt = threadIdx.x % kG;
-  // one row unit (uniform over its kG threads); called once per unit of the launch
+  // per-lane best pair keys of the wave-level pair scoring
+  __shared__ unsigned long long s_key[TB];
+  const uint32_t tid = threadIdx.x;
+  // one row unit (workgroup-uniform); called once per unit of the launch
   auto unit = [&](const int64_t ru) {
-    if (ru >= w.RU) return;
     const int r = (int)(ru % w.R);
     const bool inner = r >= 1 && r <= w.R - 2;
     // every row offset and both neighbour grids in one round of loads
@@ -1254,131 +1413,112 @@ __global__ __launch_bounds__(TB) void k_links(Ws w) {
     const uint32_t endu = w.ru_off[inner ? ru + 2 : ru + 1];
     const GridParams Gd = w.grid[rdn], Gu = w.grid[rup];
     const uint32_t n = offu - off;
-    if (n == 0) return;
     // edge rows have no links; an over-full row unit (reported as an error) gets none either
     if (!inner || n > (uint32_t)kMaxRow) {
-      if (kClass == 2)   // (written by one of the instantiations)
-        for (uint32_t k = gt; k < n; k += kG) { w.up[off + k] = -1; w.dn[off + k] = -1; }
+      for (uint32_t k = tid; k < n; k += TB) { w.up[off + k] = -1; w.dn[off + k] = -1; }
       return;
     }
     const uint32_t nd = off - offd, nu = endu - offu;
-    const int cls = links_class(n, nd, nu, true);
-    if (cls != kClass) return;
-    const bool lds = nd <= kS && nu <= kS;
-    float4* sd = s_d[g];
-    float4* su = s_u[g];
-    uint16_t* scd = s_cd[g];
-    uint16_t* scu = s_cu[g];
+    const bool lds = nd <= kSlab && nu <= kSlab;
     // this thread's own clusters (grid order) for its first rounds, read now
     // so that they arrive with the staged rows
-    constexpr int kOwn = 4;   // (the slab variant's rounds shift through four)
+    constexpr int kOwn = 4;
     float4 mine[kOwn];
   #pragma unroll
     for (int i = 0; i < kOwn; ++i) {
-      const uint32_t k = gt + kG * i;
+      const uint32_t k = tid + TB * i;
       mine[i] = w.gbuf[off + (k < n ? k : 0u)];   // (used only if k < n)
     }
-    if (lds) {
-      // all of a thread's staging loads are issued before the first LDS store
-      // (one memory round trip instead of one per loop iteration); slots past
-      // a row's end load an entry known to exist (this row's first entry, the
-      // row's first cell offset) and store it to the spare slot, so that
-      // neither the loads nor the stores need a branch
-      constexpr int kE = (int)((kS + kG - 1) / kG);                          // entries per thread
-      constexpr int kC = (int)((kCellsPerCluster * kS + 1 + kG) / kG);      // cell offsets per thread
-      const uint32_t ncd = Gd.nz() * Gd.ny(), ncu = Gu.nz() * Gu.ny();
-  #pragma unroll
-      for (int j = 0; j < kE; ++j) {
-        const uint32_t i = gt + kG * (uint32_t)j;
-        const float4 a = w.gbuf[i < nd ? offd + i : off];
-        const float4 b = w.gbuf[i < nu ? offu + i : off];
-        sd[i < nd ? i : kSpareE] = a;
-        su[i < nu ? i : kSpareE] = b;
-      }
-  #pragma unroll
-      for (int j = 0; j < kC; ++j) {
-        const uint32_t i = gt + kG * (uint32_t)j;
-        const uint16_t a = w.cell_off[Gd.cell_base + (i <= ncd ? i : 0u)];
-        const uint16_t b = w.cell_off[Gu.cell_base + (i <= ncu ? i : 0u)];
-        scd[i <= ncd ? i : kSpareC] = a;
-        scu[i <= ncu ? i : kSpareC] = b;
-      }
-      if (kG == TB) __syncthreads(); else wave_sync();
-    }
-    uint16_t* ld = s_ld + kCand * threadIdx.x;
-    uint16_t* lu = s_lu + kCand * threadIdx.x;
     const float WY = w.P.win_y, WZ = w.P.win_z;
-    auto link = [&](const float4& me) {
-      const uint32_t p = __float_as_uint(me.w);
-      const float xi = me.z, yi = me.x, zi = me.y;
-      int32_t bu = -1, bd = -1;
-      if (lds) {
-        const int cd = collect(Gd, (const float4*)sd, (const uint16_t*)scd, yi, zi, WY, WZ, ld);
-        const int cu = cd > 0 ? collect(Gu, (const float4*)su, (const uint16_t*)scu, yi, zi, WY, WZ, lu) : 0;
-        if (cd <= kCand && cu <= kCand)
-          best_pair(w, xi, yi, zi, (const float4*)sd, ld, cd, (const float4*)su, lu, cu, bu, bd);
-        else
-          find_pair(w, xi, yi, zi, Gd, (const float4*)sd, (const uint16_t*)scd, Gu, (const float4*)su,
-                    (const uint16_t*)scu, bu, bd);
-      } else {
-        find_pair(w, xi, yi, zi, Gd, w.gbuf + offd, w.cell_off + Gd.cell_base, Gu, w.gbuf + offu,
+    if (!lds) {
+      auto link = [&](const float4& me) {
+        int32_t bu, bd;
+        find_pair(w, me.z, me.x, me.y, Gd, w.gbuf + offd, w.cell_off + Gd.cell_base, Gu, w.gbuf + offu,
                   w.cell_off + Gu.cell_base, bu, bd);
-      }
-      w.up[p] = bu;
-      w.dn[p] = bd;
-    };
-    if constexpr (kClass == 2) {
-      if (lds) {
-        // rounds of the wave's 64 clusters: candidate lists per lane, then
-        // the wave's pairs scored by all its lanes; a lane whose lists
-        // overflow takes find_pair afterwards
-        const uint32_t wb = gt & ~63u;
-        const uint16_t* ld_w = s_ld + kCand * (threadIdx.x & ~63u);
-        const uint16_t* lu_w = s_lu + kCand * (threadIdx.x & ~63u);
-        unsigned long long* key_w = s_key + (threadIdx.x & ~63u);
-        // the prefetched clusters move down one slot per round (an array
-        // indexed by the round would be placed in scratch memory)
-        float4 m0 = mine[0], m1 = mine[1], m2 = mine[2], m3 = mine[3];
-        for (uint32_t i = 0; wb + kG * i < n; ++i) {
-          const uint32_t k = gt + kG * i;
-          const bool has = k < n;
-          float4 me = m0;
-          if (i >= (uint32_t)kOwn) me = w.gbuf[off + (has ? k : 0u)];
-          m0 = m1; m1 = m2; m2 = m3;
-          const float xi = me.z, yi = me.x, zi = me.y;
-          int cd = 0, cu = 0;
-          if (has) {
-            cd = collect(Gd, (const float4*)sd, (const uint16_t*)scd, yi, zi, WY, WZ, ld);
-            cu = cd > 0 ? collect(Gu, (const float4*)su, (const uint16_t*)scu, yi, zi, WY, WZ, lu) : 0;
-          }
-          const bool fb = has && (cd > kCand || cu > kCand);
-          int32_t bu, bd;
-          wave_pairs(w, has && !fb, xi, yi, zi, (uint32_t)cd, (uint32_t)cu, (const float4*)sd, (const float4*)su,
-                     ld_w, lu_w, key_w, offd, offu, bu, bd);
-          if (fb)
-            find_pair(w, xi, yi, zi, Gd, (const float4*)sd, (const uint16_t*)scd, Gu, (const float4*)su,
-                      (const uint16_t*)scu, bu, bd);
-          if (has) {
-            const uint32_t p = __float_as_uint(me.w);
-            w.up[p] = bu;
-            w.dn[p] = bd;
-          }
-        }
-        return;
-      }
+        const uint32_t p = __float_as_uint(me.w);
+        w.up[p] = bu;
+        w.dn[p] = bd;
+      };
+  #pragma unroll
+      for (int i = 0; i < kOwn; ++i)
+        if (tid + TB * i < n) link(mine[i]);
+      for (uint32_t k = tid + TB * kOwn; k < n; k += TB) link(w.gbuf[off + k]);
+      return;
+    }
+    // all of a thread's staging loads are issued before the first LDS store
+    // (one memory round trip instead of one per loop iteration); slots past
+    // a row's end load an entry known to exist (this row's first entry, the
+    // row's first cell offset) and store it to the spare slot, so that
+    // neither the loads nor the stores need a branch
+    constexpr int kE = (int)((kSlab + TB - 1) / TB);                          // entries per thread
+    constexpr int kC = (int)((kCellsPerCluster * kSlab + 1 + TB) / TB);      // cell offsets per thread
+    const uint32_t ncd = Gd.nz() * Gd.ny(), ncu = Gu.nz() * Gu.ny();
+  #pragma unroll
+    for (int j = 0; j < kE; ++j) {
+      const uint32_t i = tid + TB * (uint32_t)j;
+      const float4 a = w.gbuf[i < nd ? offd + i : off];
+      const float4 b = w.gbuf[i < nu ? offu + i : off];
+      sd[i < nd ? i : kSpareE] = a;
+      su[i < nu ? i : kSpareE] = b;
     }
   #pragma unroll
-    for (int i = 0; i < kOwn; ++i)
-      if (gt + kG * i < n) link(mine[i]);
-    for (uint32_t k = gt + kG * kOwn; k < n; k += kG) link(w.gbuf[off + k]);
+    for (int j = 0; j < kC; ++j) {
+      const uint32_t i = tid + TB * (uint32_t)j;
+      const uint16_t a = w.cell_off[Gd.cell_base + (i <= ncd ? i : 0u)];
+      const uint16_t b = w.cell_off[Gu.cell_base + (i <= ncu ? i : 0u)];
+      scd[i <= ncd ? i : kSpareC] = a;
+      scu[i <= ncu ? i : kSpareC] = b;
+    }
+    __syncthreads();
+    uint16_t* ld = s_ld + kCand * tid;
+    uint16_t* lu = s_lu + kCand * tid;
+    // rounds of the wave's 64 clusters: candidate lists per lane, then
+    // the wave's pairs scored by all its lanes; a lane whose lists
+    // overflow takes find_pair afterwards
+    const uint32_t wb = tid & ~63u;
+    const uint16_t* ld_w = s_ld + kCand * wb;
+    const uint16_t* lu_w = s_lu + kCand * wb;
+    unsigned long long* key_w = s_key + wb;
+    // the prefetched clusters move down one slot per round (an array
+    // indexed by the round would be placed in scratch memory)
+    float4 m0 = mine[0], m1 = mine[1], m2 = mine[2], m3 = mine[3];
+    for (uint32_t i = 0; wb + TB * i < n; ++i) {
+      const uint32_t k = tid + TB * i;
+      const bool has = k < n;
+      float4 me = m0;
+      if (i >= (uint32_t)kOwn) me = w.gbuf[off + (has ? k : 0u)];
+      m0 = m1; m1 = m2; m2 = m3;
+      const float xi = me.z, yi = me.x, zi = me.y;
+      int cd = 0, cu = 0;
+      if (has) {
+        cd = collect<kCand>(Gd, sd, scd, yi, zi, WY, WZ, ld);
+        cu = cd > 0 ? collect<kCand>(Gu, su, scu, yi, zi, WY, WZ, lu) : 0;
+      }
+      const bool fb = has && (cd > kCand || cu > kCand);
+      int32_t bu, bd;
+      wave_pairs(w, has && !fb, xi, yi, zi, (uint32_t)cd, (uint32_t)cu, (const float4*)sd, (const float4*)su,
+                 ld_w, lu_w, key_w, offd, offu, bu, bd);
+      if (fb)
+        find_pair(w, xi, yi, zi, Gd, (const float4*)sd, (const uint16_t*)scd, Gu, (const float4*)su,
+                  (const uint16_t*)scu, bu, bd);
+      if (has) {
+        const uint32_t p = __float_as_uint(me.w);
+        w.up[p] = bu;
+        w.dn[p] = bd;
+      }
+    }
   };
-  if (kNG != 1 || !ru_lists(w.RU)) {
-    unit((int64_t)blockIdx.x * kNG + g);
-    return;
-  }
-  const uint32_t cnt = w.flags[kClass == 2 ? F_LLINKS2 : F_LLINKS1];
-  for (uint32_t i = blockIdx.x; i < cnt; i += gridDim.x) {
-    unit(kClass == 2 ? w.ru_links[w.RU - 1 - (int64_t)i] : w.ru_links[i]);
+  const bool lists = ru_lists(w.RU);
+  const uint32_t cnt = w.flags[F_LLINKS];
+  for (uint32_t i = blockIdx.x; i < (lists || cnt == 0u ? cnt : (uint32_t)w.RU); i += gridDim.x) {
+    const uint32_t ru = lists ? w.ru_links[i] : i;
+    if (!lists) {
+      const int r = (int)(ru % (uint32_t)w.R);
+      const uint32_t a = w.ru_off[r > 0 ? ru - 1 : ru], b = w.ru_off[ru], c = w.ru_off[ru + 1];
+      const uint32_t z = w.ru_off[r < w.R - 1 ? ru + 2 : ru + 1];
+      if (b == c || (z - a <= cap && b - a <= kBandRow && z - c <= kBandRow)) continue;   // (k_links_band)
+    }
+    unit(ru);
     __syncthreads();   // LDS is reused by the next unit
   }
 }
@@ -2412,9 +2552,18 @@ hipError_t run_pipeline(const Ws& w, hipStream_t st, const PhaseEvents* pe) {
   TPCCA_CHECK(hipGetLastError());
   const unsigned nbN = (unsigned)w.nb;
   TPCCA_MARK(PH_LINKS);
-  k_links<kTiny, 64><<<g_wave, TB, 0, st>>>(w);
-  k_links<kSmallSlab, TB><<<g_mid, TB, 0, st>>>(w);
-  k_links<kSlab, TB><<<g_big, TB, 0, st>>>(w);
+  // Rows of a band: with many row units eight (64 small events 315 us, with
+  // six 338, with ten 333; a 24-collision frame 93, 88 and 111); with few (one
+  // event) two, for more workgroups (0.77 M clusters 42 us with four, 36 with
+  // two; one sector's 22 k 14.5 and 10.7).  LDS for one and a half times the
+  // band that an average row would make, within limits (a single event:
+  // fixed, as one sector may hold all of it).
+  const int lr = lists ? kLinkRows : 2;
+  const int64_t want = lists ? (3 * (lr + 2) * (w.N / w.RU + 1) / 2 + 63) / 64 * 64 : 768;
+  const uint32_t lcap = (uint32_t)std::min<int64_t>(std::max<int64_t>(want, kLinkEMin), kLinkE);
+  k_links_band<<<(unsigned)((int64_t)w.E * w.S * ((w.R + lr - 1) / lr)), TB,
+                 lcap * sizeof(float4) + link_words(lcap) * sizeof(uint32_t), st>>>(w, lr, lcap);
+  k_links<<<g_big, TB, 0, st>>>(w, lcap);
   TPCCA_MARK(PH_CLEAN);
   k_clean<<<nbN, TB, 0, st>>>(w);
   TPCCA_MARK(PH_COMPACT);

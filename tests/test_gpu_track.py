@@ -528,3 +528,26 @@ def test_batch_with_bands_above_the_small_ownership_class(tracker, orc):
     for ev, out in zip((big, small, big, small), tracker.track_batch([to_dev(e) for e in (big, small, big, small)])):
         compare(ev, out, None, orc.track(ev, precision=32), check_taps=False)
         assert out.n_tracks > 0
+
+
+def test_link_rows_at_the_band_limits(tracker, orc):
+    """Neighbouring rows at the edges of what the band link kernel takes (256
+    clusters in a neighbour, 768 and 1,152 in three rows), windows with 15 to
+    17 candidates a side, empty rows and the edge rows: links and tracks of
+    the event alone and in a batch equal the oracle."""
+    ev = synth.make_event(seed=71, n_primaries=60, noise=0.0, single_sector=True)
+    have = np.bincount(ev.row, minlength=ev.geom.n_rows)
+    want = {0: 40, 1: 60, 10: 255, 11: 30, 12: 256, 13: 257, 14: 30, 15: 256, 16: 256, 17: 256, 18: 256, 19: 255,
+            30: 384, 31: 384, 32: 384, 33: 385, 40: 256, 41: 640, 42: 256, 43: 10, 157: 60, 158: 80}
+    patches = [(r, n - int(have[r]), (-9.0, 9.0), (30.0, 200.0)) for r, n in want.items() if n > have[r]]
+    patches += [(r, n, (-0.5, 0.5), (99.5, 100.5)) for r, n in
+                zip(range(60, 72), (15, 16, 17, 16, 1, 17, 17, 15, 16, 16, 40, 16))]
+    ev = _with_patches(ev, patches, seed=72)
+    print(f"[gpu] link bands n={ev.n}", flush=True)
+    ref = orc.track(ev, precision=32)
+    t = to_dev(ev)
+    out = tracker.track(*t, taps=True)
+    compare(ev, out, tracker.debug_tracklets(), ref)
+    for b in tracker.track_batch([t] * 4, taps=True):
+        compare(ev, b, None, ref)
+    assert out.n_tracks > 0
