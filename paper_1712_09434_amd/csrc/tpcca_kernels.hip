@@ -1777,18 +1777,41 @@ __device__ __forceinline__ bool accepted(float X, const Acc& a, const float p[5]
 // and roots take the short sequences.  On one sector's 17 k clusters the
 // kernel takes 277 us (476 with one lane per seed, a test per loaded entry
 // and no L2 warming), on 0.77 M clusters 345 (494), on 3.8 M, where three
-// waves per SIMD share the issue slots, 770 (805).
-// Lanes that have finished wait until a quarter of the wave does (or the
-// whole wave has): then they write their tracklets and take the next seeds
-// from a device counter (one atomic per wave).  The seed list is split into
-// kXcd contiguous ranges with a counter each; a workgroup starts on the
-// range of its XCD and moves on to the others once that one is used up.
+// waves per SIMD share the issue slots, 711 (805).
+// With several lanes per seed, groups that have finished wait until a quarter
+// of the wave does (or the whole wave has): then they write their tracklets
+// and take the next seeds from a device counter (one atomic per wave).  The
+// seed list is split into kXcd contiguous ranges with a counter each; a
+// workgroup starts on the range of its XCD and moves on to the others once
+// that one is used up.
 enum : int { ST_CHAIN = 0, ST_UP = 1, ST_BACK = 2, ST_DOWN = 3, ST_DONE = 4, ST_IDLE = 5 };
+
+// With one lane per seed the workgroup's waves are regrouped as lanes finish:
+// every kRegroupEvery steps the live lanes are counted, and once fewer waves
+// can hold them the lanes of the others move, through LDS, into the idle
+// lanes of these (which waves go turns with the chunk, as a workgroup's
+// waves lie on different SIMDs).  Seeds last between 17 and 167 steps, so
+// waves that keep their lanes to the end run with 0.62 to 0.76 of them; lanes
+// that take new seeds instead bring the steps of all phases (and the three
+// long updates of a seed's start) into every step of the wave.  3.8 M
+// clusters 775 -> 711 us, 64 small events 783 -> 773; counting every 4 steps
+// 733 and 791, every 8 steps 716 and 780.
+struct Regroup {
+  static constexpr int kMoved = 128;   // lanes moved at once, at most
+  static constexpr int kWords = 28;    // words of a lane's state
+  uint32_t cnt[2][TB / 64];
+  uint32_t state[kWords * kMoved];
+};
+constexpr uint32_t kRegroupEvery = 16;
+// chunks of TB seeds of the largest of kXcd ranges
+__device__ __forceinline__ uint32_t regroup_chunks(uint32_t ns) {
+  return ((ns + kXcd - 1u) / kXcd + TB - 1u) / TB;
+}
 
 // G lanes per seed: every lane of a group holds the same state (the same
 // expressions of the same values), the row search is shared out.
 template <int G>
-__device__ __forceinline__ void tracklets_wave(const Ws& w, const float* sX, const uint32_t ns) {
+__device__ __forceinline__ void tracklets_wave(const Ws& w, const float* sX, const uint32_t ns, Regroup& grp) {
   const Acc acc{w.tan_a, w.z_max};
   const int R = w.R;
   const int gl = lane_id() & (G - 1);
@@ -1846,92 +1869,64 @@ __device__ __forceinline__ void tracklets_wave(const Ws& w, const float* sX, con
       wmask |= 1u << q;
     }
   };
-  // seed range of this workgroup's XCD (workgroups are dispatched to the
-  // XCDs round-robin), so that each XCD's L2 holds the grids of its sectors
-  int rx = (int)(blockIdx.x % kXcd), tries = 0;
-  while (true) {
-    // every lane's steps are bounded (rows only move one way per phase), so
-    // this cap is never reached by a correct kernel; it turns a defect into
-    // an error instead of a hang
-    if (++iters > (1u << 22)) { atomicOr(&w.flags[F_ERR], ERR_STUCK); break; }
-    const uint64_t act = __ballot(phase < ST_DONE);
-    // refills stall the whole wave (counter, atomic, seed set-up): take new
-    // seeds only once a quarter of the lanes wait, or no lane is working
-    if (act == 0ull || (more && 64 - __popcll(act) >= kRefillMin)) {
-      if (phase == ST_DONE) {
-        if (G == 1 && wmask) flush();
-        if (gl == 0) {
-          float* st = w.tl_state + (int64_t)s * kTl;
+  // writes the finished tracklet
+  auto finish = [&]() {
+    if (G == 1 && wmask) flush();
+    if (gl == 0) {
+      float* st = w.tl_state + (int64_t)s * kTl;
 #pragma unroll
-          for (int i = 0; i < 5; ++i) st[i] = p[i];
+      for (int i = 0; i < 5; ++i) st[i] = p[i];
 #pragma unroll
-          for (int i = 0; i < 15; ++i) st[5 + i] = C[i];
-          w.tl_nhits[s] = nhits;
-          w.tl_range[s] = rlo | (rhi << 16);
-          w.tl_key[s] = ((uint64_t)(uint32_t)nhits << 40) | ((uint64_t)(255 - r0) << 32) |
-                        (uint64_t)(0xFFFFFFFFu - w.cid[h0]);
-        }
-        phase = ST_IDLE;
-      }
-      bool want = phase == ST_IDLE;
-      uint64_t wm = more ? __ballot(want) : 0ull;
-      while (wm) {
-        const uint32_t lo = (uint32_t)(((uint64_t)ns * (uint32_t)rx) / kXcd);
-        const uint32_t hi = (uint32_t)(((uint64_t)ns * (uint32_t)(rx + 1)) / kXcd);
-        uint32_t* ctr = &w.flags[F_SEEDCTR + rx];
-        // a fresh (L2-bypassing) read first: exhausted ranges cost no atomic
-        uint32_t base = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (base < hi - lo) {
-          const int leader = __ffsll((unsigned long long)wm) - 1;
-          if (lane_id() == leader) base = atomicAdd(ctr, (uint32_t)__popcll(wm) / G);
-          base = __shfl(base, leader, 64);
-          if (want) {
-            const uint64_t mine = (uint64_t)lo + base + (uint32_t)__popcll(wm & groups_before) / G;
-            if (mine < hi) {
-              want = false;
-              s = (uint32_t)mine;
-              h0 = (int32_t)w.seeds[s];
-              const uint32_t ru0 = w.cru[h0];
-              r0 = (int)(ru0 % (uint32_t)R);
-              rubase = ru0 - (uint32_t)r0;
-              const float4 a0 = w.cpk[h0];
-              const int32_t h1 = __float_as_int(a0.w);
-              const float4 a1 = w.cpk[h1];
-              const int32_t h2 = __float_as_int(a1.w);
-              const float4 a2 = w.cpk[h2];
-              float sdir, tdir;
-              const float x0 = a0.x, y0 = a0.y, z0 = a0.z;
-              chord_dir(x0, y0, z0, a2.x, a2.y, a2.z, sdir, tdir);
-              p[0] = y0; p[1] = z0; p[2] = sdir; p[3] = tdir; p[4] = 0.0f;
-              init_cov(C, w.m.vy, w.m.vz);
-              nupd = 0;
-              rlo = rhi = rstate = r0;
-              xc = x0;
-              hits = w.tl_hits + (int64_t)s * 8;
-              wbase = -1;
-              if (fabsf(sdir) < w.m.sin_max) {
-                put(r0, h0);
-                nhits = 1;
-                nxt = h1;
-                cn = a1;
-                phase = ST_CHAIN;
-              } else {
-                nhits = 0;
-                phase = ST_DONE;
-              }
-            }
-          }
-        }
-        wm = __ballot(want);
-        if (wm) {
-          // this range is used up: take seeds from the next one
-          if (++tries >= kXcd) { more = false; break; }   // every range is used up
-          rx = (rx + 1) % kXcd;
-        }
-      }
-      if (__ballot(phase != ST_IDLE) == 0ull) break;
+      for (int i = 0; i < 15; ++i) st[5 + i] = C[i];
+      w.tl_nhits[s] = nhits;
+      w.tl_range[s] = rlo | (rhi << 16);
+      w.tl_key[s] = ((uint64_t)(uint32_t)nhits << 40) | ((uint64_t)(255 - r0) << 32) |
+                    (uint64_t)(0xFFFFFFFFu - w.cid[h0]);
     }
-    if (phase >= ST_DONE) continue;
+    phase = ST_IDLE;
+  };
+  // sets the lane up for seed s
+  auto begin = [&]() {
+    h0 = (int32_t)w.seeds[s];
+    const uint32_t ru0 = w.cru[h0];
+    r0 = (int)(ru0 % (uint32_t)R);
+    rubase = ru0 - (uint32_t)r0;
+    const float4 a0 = w.cpk[h0];
+    const int32_t h1 = __float_as_int(a0.w);
+    const float4 a1 = w.cpk[h1];
+    const int32_t h2 = __float_as_int(a1.w);
+    const float4 a2 = w.cpk[h2];
+    float sdir, tdir;
+    const float x0 = a0.x, y0 = a0.y, z0 = a0.z;
+    chord_dir(x0, y0, z0, a2.x, a2.y, a2.z, sdir, tdir);
+    p[0] = y0; p[1] = z0; p[2] = sdir; p[3] = tdir; p[4] = 0.0f;
+    init_cov(C, w.m.vy, w.m.vz);
+    nupd = 0;
+    rlo = rhi = rstate = r0;
+    xc = x0;
+    hits = w.tl_hits + (int64_t)s * 8;
+    wbase = -1;
+    if (fabsf(sdir) < w.m.sin_max) {
+      put(r0, h0);
+      nhits = 1;
+      nxt = h1;
+      cn = a1;
+      phase = ST_CHAIN;
+    } else {
+      nhits = 0;
+      phase = ST_DONE;
+    }
+  };
+  // the next step's inputs
+  auto ahead = [&]() {
+    if (phase == ST_CHAIN) {
+      cn = w.cpk[nxt];
+    } else if (phase < ST_DONE) {
+      Xr = sX[r];
+      Q = w.grid[rubase + (uint32_t)r];
+    }
+  };
+  auto step = [&]() {
     // one row step: every active lane transports once (the target plane
     // depends on the phase), then the phase's own work follows
     const bool chain = phase == ST_CHAIN;
@@ -2006,13 +2001,7 @@ __device__ __forceinline__ void tracklets_wave(const Ws& w, const float* sX, con
         }
       }
     }
-    // the next step's inputs, in flight during the update
-    if (phase == ST_CHAIN) {
-      cn = w.cpk[nxt];
-    } else if (phase < ST_DONE) {
-      Xr = sX[r];
-      Q = w.grid[rubase + (uint32_t)r];
-    }
+    ahead();   // (in flight during the update)
     if (wr) put(prow, pval);
     if (upd) {
       float dummy = 0.0f;
@@ -2020,6 +2009,132 @@ __device__ __forceinline__ void tracklets_wave(const Ws& w, const float* sX, con
       else update(p, C, my, mz, w.m, dummy);
       ++nupd;
     }
+  };
+  if constexpr (G == 1) {
+    // a workgroup's 256 consecutive seeds at a time, the chunks of an XCD's
+    // range on that XCD
+    const int wv = threadIdx.x >> 6;
+    const uint32_t nchunk = kXcd * regroup_chunks(ns);
+    uint32_t par = 0;
+    for (uint32_t c = blockIdx.x; c < nchunk; c += gridDim.x) {
+      const uint32_t x = c % kXcd, hi = (uint32_t)(((uint64_t)ns * (x + 1)) / kXcd);
+      s = (uint32_t)(((uint64_t)ns * x) / kXcd) + c / kXcd * TB + threadIdx.x;
+      phase = ST_IDLE;
+      if (s < hi) begin();
+      const int rot = (int)(c / kXcd + c / (32 * kXcd)) & 3;
+      const int pw = (wv - rot) & 3;   // the wave's turn to be given up is last for 0
+      int kept = TB / 64;
+      iters = 0;
+      while (true) {
+        // (at most 2 R + 16 steps; a defect is an error instead of a hang)
+        if (++iters > (1u << 22)) { atomicOr(&w.flags[F_ERR], ERR_STUCK); return; }
+        if (phase < ST_DONE) step();
+        if (iters % kRegroupEvery != 0u) continue;
+        if (phase == ST_DONE) finish();
+        const uint64_t live = __ballot(phase < ST_DONE);
+        par ^= 1u;
+        if (lane_id() == 0) grp.cnt[par][pw] = (uint32_t)__popcll(live);
+        __syncthreads();
+        uint32_t cnt[TB / 64], total = 0;
+#pragma unroll
+        for (int q = 0; q < TB / 64; ++q) { cnt[q] = grp.cnt[par][q]; total += cnt[q]; }
+        if (total == 0u) break;
+        const int need = (int)((total + 63u) >> 6);
+        if (need >= kept) continue;
+        kept = need;
+        uint32_t first = 0, moved = 0;
+#pragma unroll
+        for (int q = 0; q < TB / 64; ++q) {
+          if (q >= kept) moved += cnt[q];
+          if (q < pw && (q < kept) == (pw < kept)) first += q < kept ? 64u - cnt[q] : cnt[q];
+        }
+        const bool keep = pw < kept;
+        const uint32_t at = first + (uint32_t)__popcll((keep ? ~live : live) & lanemask_lt());
+        if (!keep && phase < ST_DONE) {
+          if (wmask) flush();
+          uint32_t* q = grp.state + at;
+          auto put_u = [&](int i, uint32_t v) { q[i * Regroup::kMoved] = v; };
+          put_u(0, s); put_u(1, (uint32_t)h0); put_u(2, (uint32_t)nxt); put_u(3, rubase);
+          put_u(4, (uint32_t)r0 | ((uint32_t)r & 255u) << 8 | (uint32_t)rstate << 16 | (uint32_t)phase << 24);
+          put_u(5, (uint32_t)rlo | (uint32_t)rhi << 8 | (uint32_t)gap << 16);
+          put_u(6, (uint32_t)nhits | (uint32_t)nupd << 16);
+          put_u(7, __float_as_uint(xc));
+#pragma unroll
+          for (int i = 0; i < 5; ++i) put_u(8 + i, __float_as_uint(p[i]));
+#pragma unroll
+          for (int i = 0; i < 15; ++i) put_u(13 + i, __float_as_uint(C[i]));
+          phase = ST_IDLE;
+        }
+        __syncthreads();
+        if (keep && phase >= ST_DONE && at < moved) {
+          const uint32_t* q = grp.state + at;
+          auto get_u = [&](int i) { return q[i * Regroup::kMoved]; };
+          s = get_u(0); h0 = (int32_t)get_u(1); nxt = (int32_t)get_u(2); rubase = get_u(3);
+          const uint32_t a = get_u(4), b = get_u(5), d = get_u(6);
+          r0 = (int)(a & 255u); r = (int)(a >> 8 & 255u); rstate = (int)(a >> 16 & 255u); phase = (int)(a >> 24);
+          rlo = (int)(b & 255u); rhi = (int)(b >> 8 & 255u); gap = (int)(b >> 16);
+          nhits = (int)(d & 0xFFFFu); nupd = (int)(d >> 16);
+          xc = __uint_as_float(get_u(7));
+#pragma unroll
+          for (int i = 0; i < 5; ++i) p[i] = __uint_as_float(get_u(8 + i));
+#pragma unroll
+          for (int i = 0; i < 15; ++i) C[i] = __uint_as_float(get_u(13 + i));
+          hits = w.tl_hits + (int64_t)s * 8;
+          wbase = -1;
+          wmask = 0;
+          ahead();
+        }
+      }
+    }
+    return;
+  }
+  // seed range of this workgroup's XCD (workgroups are dispatched to the
+  // XCDs round-robin), so that each XCD's L2 holds the grids of its sectors
+  int rx = (int)(blockIdx.x % kXcd), tries = 0;
+  while (true) {
+    // every lane's steps are bounded (rows only move one way per phase), so
+    // this cap is never reached by a correct kernel; it turns a defect into
+    // an error instead of a hang
+    if (++iters > (1u << 22)) { atomicOr(&w.flags[F_ERR], ERR_STUCK); break; }
+    const uint64_t act = __ballot(phase < ST_DONE);
+    // refills stall the whole wave (counter, atomic, seed set-up): take new
+    // seeds only once a quarter of the lanes wait, or no lane is working
+    if (act == 0ull || (more && 64 - __popcll(act) >= kRefillMin)) {
+      if (phase == ST_DONE) {
+        finish();
+      }
+      bool want = phase == ST_IDLE;
+      uint64_t wm = more ? __ballot(want) : 0ull;
+      while (wm) {
+        const uint32_t lo = (uint32_t)(((uint64_t)ns * (uint32_t)rx) / kXcd);
+        const uint32_t hi = (uint32_t)(((uint64_t)ns * (uint32_t)(rx + 1)) / kXcd);
+        uint32_t* ctr = &w.flags[F_SEEDCTR + rx];
+        // a fresh (L2-bypassing) read first: exhausted ranges cost no atomic
+        uint32_t base = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (base < hi - lo) {
+          const int leader = __ffsll((unsigned long long)wm) - 1;
+          if (lane_id() == leader) base = atomicAdd(ctr, (uint32_t)__popcll(wm) / G);
+          base = __shfl(base, leader, 64);
+          if (want) {
+            const uint64_t mine = (uint64_t)lo + base + (uint32_t)__popcll(wm & groups_before) / G;
+            if (mine < hi) {
+              want = false;
+              s = (uint32_t)mine;
+              begin();
+            }
+          }
+        }
+        wm = __ballot(want);
+        if (wm) {
+          // this range is used up: take seeds from the next one
+          if (++tries >= kXcd) { more = false; break; }   // every range is used up
+          rx = (rx + 1) % kXcd;
+        }
+      }
+      if (__ballot(phase != ST_IDLE) == 0ull) break;
+    }
+    if (phase >= ST_DONE) continue;
+    step();
   }
 }
 
@@ -2054,13 +2169,14 @@ constexpr unsigned kWarmGrid = 512;
 
 __global__ __launch_bounds__(TB) void k_tracklets(Ws w) {
   __shared__ float sX[256];
+  __shared__ Regroup grp;
   for (int r = threadIdx.x; r < w.R; r += TB) sX[r] = w.row_x[r];
   __syncthreads();
   const uint32_t ns = w.flags[F_NSEEDS];
   const int G = tracklet_lanes(ns);
   // when the lanes of the lower workgroups already outnumber the seeds they
   // take (and, by refills, finish) them all: this one has no seeds to take
-  const int64_t busy = ((int64_t)ns + TB / G - 1) / (TB / G);
+  const int64_t busy = G == 1 ? (int64_t)kXcd * regroup_chunks(ns) : ((int64_t)ns + TB / G - 1) / (TB / G);
   if ((int64_t)blockIdx.x >= busy) {
     const uint32_t x = blockIdx.x % kXcd;
     const uint32_t lo = (uint32_t)(((uint64_t)ns * x) / kXcd), hi = (uint32_t)(((uint64_t)ns * (x + 1)) / kXcd);
@@ -2078,9 +2194,9 @@ __global__ __launch_bounds__(TB) void k_tracklets(Ws w) {
     touch_lines(w.gbuf + c0, (c1 - c0) * 16, t, nt);
     return;
   }
-  if (G == 8) tracklets_wave<8>(w, sX, ns);
-  else if (G == 4) tracklets_wave<4>(w, sX, ns);
-  else tracklets_wave<1>(w, sX, ns);
+  if (G == 8) tracklets_wave<8>(w, sX, ns, grp);
+  else if (G == 4) tracklets_wave<4>(w, sX, ns, grp);
+  else tracklets_wave<1>(w, sX, ns, grp);
 }
 
 // ----------------------------------------------------------- a6: selection
