@@ -1694,6 +1694,15 @@ __device__ __forceinline__ Found search_row(const Ws& w, const GridParams& Q, co
   const uint32_t a0 = ca[iy0], a1 = ca[iy1], b0 = cb[iy0], b1 = cb[iy1];
   const uint32_t na = a1 - a0, nb = nzr > 1u ? b1 - b0 : 0u;
   if constexpr (G == 1) {
+    // entries k .. n - 1 of e, four loads at a time (wide windows, most of a
+    // seed's first steps, hold many: one load per trip kept whole waves
+    // waiting, 64 small events 773 us instead of 716)
+    auto rest = [&](const float4* e, uint32_t k, uint32_t n) {
+      for (; k < n; k += 4u) {
+        const float4 c0 = e[k], c1 = e[k + 1u], c2 = e[k + 2u], c3 = e[k + 3u];
+        consider(c0, true); consider(c1, k + 1u < n); consider(c2, k + 2u < n); consider(c3, k + 3u < n);
+      }
+    };
     const float4* ga = g + a0;
     const float4* gb = g + b0;
     const float4 A0 = ga[0], A1 = ga[1], B0 = gb[0], B1 = gb[1];
@@ -1701,15 +1710,17 @@ __device__ __forceinline__ Found search_row(const Ws& w, const GridParams& Q, co
       const float4 A2 = ga[2], A3 = ga[3], B2 = gb[2], B3 = gb[3];
       consider(A2, na > 2u); consider(A3, na > 3u);
       consider(B2, nb > 2u); consider(B3, nb > 3u);
-      for (uint32_t k = 4; k < na; ++k) consider(ga[k], true);
-      for (uint32_t k = 4; k < nb; ++k) consider(gb[k], true);
+      rest(ga, 4u, na);
+      rest(gb, 4u, nb);
     }
     consider(A0, na > 0u); consider(A1, na > 1u);
     consider(B0, nb > 0u); consider(B1, nb > 1u);
-    for (uint32_t iz = 2; iz < nzr; ++iz) {
+    for (uint32_t iz = 2; iz < nzr; iz += 2) {
       const uint16_t* cz = ca + iz * ny;
-      const uint32_t k0 = cz[iy0], k1 = cz[iy1];
-      for (uint32_t k = k0; k < k1; ++k) consider(g[k], true);
+      const uint16_t* cy = cz + (iz + 1u < nzr ? ny : 0u);
+      const uint32_t k0 = cz[iy0], k1 = cz[iy1], m0 = cy[iy0], m1 = cy[iy1];
+      rest(g, k0, k1);
+      if (iz + 1u < nzr) rest(g, m0, m1);
     }
   } else {
     constexpr uint32_t H = G / 2;
@@ -1775,9 +1786,9 @@ __device__ __forceinline__ bool accepted(float X, const Acc& a, const float p[5]
 // step's plane, grid and chain record are loaded before the update, which
 // covers their latency; phase changes are settled in one place; quotients
 // and roots take the short sequences.  On one sector's 17 k clusters the
-// kernel takes 277 us (476 with one lane per seed, a test per loaded entry
+// kernel takes 285 us (476 with one lane per seed, a test per loaded entry
 // and no L2 warming), on 0.77 M clusters 345 (494), on 3.8 M, where three
-// waves per SIMD share the issue slots, 711 (805).
+// waves per SIMD share the issue slots, 708 (805).
 // With several lanes per seed, groups that have finished wait until a quarter
 // of the wave does (or the whole wave has): then they write their tracklets
 // and take the next seeds from a device counter (one atomic per wave).  The
@@ -2167,7 +2178,9 @@ __device__ __forceinline__ void touch_lines(const void* p, int64_t bytes, int64_
 constexpr int64_t kWarmBytes = (int64_t)3 << 20;
 constexpr unsigned kWarmGrid = 512;
 
-__global__ __launch_bounds__(TB) void k_tracklets(Ws w) {
+// (four waves per SIMD: with 129 registers, three, 3.8 M clusters take 1,056 us
+// instead of 708)
+__global__ __launch_bounds__(TB, 4) void k_tracklets(Ws w) {
   __shared__ float sX[256];
   __shared__ Regroup grp;
   for (int r = threadIdx.x; r < w.R; r += TB) sX[r] = w.row_x[r];

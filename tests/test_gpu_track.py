@@ -551,3 +551,27 @@ def test_link_rows_at_the_band_limits(tracker, orc):
     for b in tracker.track_batch([t] * 4, taps=True):
         compare(ev, b, None, ref)
     assert out.n_tracks > 0
+
+
+@pytest.mark.parametrize("grid", [3, 61, 4096])
+def test_regrouped_seeds_with_any_grid(tracker, orc, grid):
+    """Above 32,768 seeds a workgroup takes chunks of 256 seeds and moves its
+    live lanes into fewer waves as others finish: tracklets of very different
+    lengths (a few rows to all), any number of chunks per workgroup and a
+    partly filled last chunk give the oracle's tracks."""
+    ev = _clumped_event()
+    t = to_dev(ev)
+    tracker.track(*t, taps=True)
+    copies = -(-32769 // len(tracker.debug_tracklets()["seed_start"])) + 1
+    ref = orc.track(ev, precision=32)
+    tracker.set_tuning(tracklet_grid=grid)
+    try:
+        print(f"[gpu] {copies} copies, {grid} workgroups", flush=True)
+        batch = tracker.track_batch([t] * copies)
+    finally:
+        tracker.set_tuning()
+    for e in (0, copies // 3, copies - 1):
+        compare(ev, batch[e], None, ref, check_taps=False)
+    for b in batch:
+        for k in ("hit_off", "hit_id", "p", "cov", "chi2", "k_prior"):
+            assert torch.equal(getattr(b, k), getattr(batch[0], k)), k
