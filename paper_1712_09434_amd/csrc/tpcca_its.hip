@@ -95,7 +95,7 @@ struct ItsWs {
   float* cR;
   uint32_t* err;           // [1] bit 0: a bad layer / stave or a non-finite coordinate
   uint32_t* scnt;          // [E * kPerEv + 1] clusters per (event, layer, stave) -> offsets
-  uint32_t* scur;          // [E * kPerEv] fill cursors
+  uint32_t* rank;          // [n] place of a cluster within its stave
   uint32_t* slist;         // [n] cluster ids by stave
   float4* sA;              // [n] by stave: global X, Y, radius, z (pair tests)
   float4* sB;              // [n] by stave: local y, z, id bits (cluster search)
@@ -138,42 +138,72 @@ __global__ __launch_bounds__(TB) void k_its_init(ItsWs w) {
   if (i == 0) w.err[0] = 0u;
 }
 
-__global__ __launch_bounds__(TB) void k_its_gather(ItsWs w) {
-  const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-  if (i >= w.n) return;
-  const int e = event_of(w, i);
-  const ItsEvIn& v = w.ev[e];
-  const int64_t j = i - v.off;
-  const int l = v.layer[j], k = v.stave[j];
-  const float x = v.x[j], y = v.y[j], z = v.z[j];
-  w.cx[i] = x; w.cy[i] = y; w.cz[i] = z; w.cl[i] = (int8_t)l; w.ck[i] = (int16_t)k; w.cev[i] = e;
-  const bool ok = l >= 0 && l < kLayers && k >= 0 && k < w.ns[l] && isfinite(x) && isfinite(y) && isfinite(z);
-  w.l0f[i] = ok && l == 0 ? 1u : 0u;
-  if (!ok) {
-    atomicOr(w.err, 1u);
-    w.cX[i] = 0.0f; w.cY[i] = 0.0f; w.cR[i] = 0.0f;
-    w.cl[i] = -1;   // (skipped by the later kernels)
-    return;
-  }
-  const float ca = w.tab->ca[l][k], sa = w.tab->sa[l][k];
-  const float X = x * ca - y * sa;
-  const float Y = x * sa + y * ca;
-  w.cX[i] = X;
-  w.cY[i] = Y;
-  w.cR[i] = sqrtf(X * X + Y * Y);
-  atomicAdd(&w.scnt[sidx(e, l, k)], 1u);
-}
+// Clusters per thread and workgroup of the gather.  The staves of the
+// workgroup's first event are counted in LDS, with one global addition per
+// stave that has clusters: it returns where the workgroup's clusters begin
+// in the stave, so each cluster's place is known and the fill needs no
+// counters (20 central events: gather, cursors and fill 55 us with an
+// addition per cluster in both, 29 this way).
+constexpr int kPerThr = 4;
 
-__global__ __launch_bounds__(TB) void k_its_cursors(ItsWs w) {
-  const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-  if (i < (int64_t)w.E * kPerEv) w.scur[i] = w.scnt[i];
+__global__ __launch_bounds__(TB) void k_its_gather(ItsWs w) {
+  __shared__ uint32_t s_n[kPerEv];
+  const int64_t i0 = (int64_t)blockIdx.x * (kPerThr * TB);
+  if (i0 >= w.n) return;   // (workgroup-uniform)
+  for (int b = threadIdx.x; b < kPerEv; b += TB) s_n[b] = 0u;
+  const int e0 = event_of(w, i0);
+  __syncthreads();
+  int slot[kPerThr];        // the LDS counter, or -1
+  uint32_t rank[kPerThr];
+#pragma unroll
+  for (int k = 0; k < kPerThr; ++k) {
+    const int64_t i = i0 + k * TB + threadIdx.x;
+    slot[k] = -1;
+    rank[k] = 0u;
+    if (i >= w.n) continue;
+    const int e = w.ev[e0 + 1].off > i ? e0 : event_of(w, i);
+    const ItsEvIn& v = w.ev[e];
+    const int64_t j = i - v.off;
+    const int l = v.layer[j], st = v.stave[j];
+    const float x = v.x[j], y = v.y[j], z = v.z[j];
+    w.cx[i] = x; w.cy[i] = y; w.cz[i] = z; w.cl[i] = (int8_t)l; w.ck[i] = (int16_t)st; w.cev[i] = e;
+    const bool ok = l >= 0 && l < kLayers && st >= 0 && st < w.ns[l] && isfinite(x) && isfinite(y) && isfinite(z);
+    w.l0f[i] = ok && l == 0 ? 1u : 0u;
+    if (!ok) {
+      atomicOr(w.err, 1u);
+      w.cX[i] = 0.0f; w.cY[i] = 0.0f; w.cR[i] = 0.0f;
+      w.cl[i] = -1;   // (skipped by the later kernels)
+      continue;
+    }
+    const float ca = w.tab->ca[l][st], sa = w.tab->sa[l][st];
+    const float X = x * ca - y * sa;
+    const float Y = x * sa + y * ca;
+    w.cX[i] = X;
+    w.cY[i] = Y;
+    w.cR[i] = sqrtf(X * X + Y * Y);
+    if (e == e0) {
+      slot[k] = sidx(0, l, st);
+      rank[k] = atomicAdd(&s_n[slot[k]], 1u);
+    } else {
+      rank[k] = atomicAdd(&w.scnt[sidx(e, l, st)], 1u);
+    }
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < kPerEv; b += TB)
+    if (s_n[b]) s_n[b] = atomicAdd(&w.scnt[e0 * kPerEv + b], s_n[b]);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kPerThr; ++k) {
+    const int64_t i = i0 + k * TB + threadIdx.x;
+    if (i < w.n) w.rank[i] = rank[k] + (slot[k] >= 0 ? s_n[slot[k]] : 0u);
+  }
 }
 
 __global__ __launch_bounds__(TB) void k_its_fill(ItsWs w) {
   const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
   if (i >= w.n || w.cl[i] < 0) return;
   const int l = w.cl[i];
-  const uint32_t pos = atomicAdd(&w.scur[sidx(w.cev[i], l, w.ck[i])], 1u);
+  const uint32_t pos = w.scnt[sidx(w.cev[i], l, w.ck[i])] + w.rank[i];
   w.slist[pos] = (uint32_t)i;
   w.sA[pos] = make_float4(w.cX[i], w.cY[i], w.cR[i], w.cz[i]);
   w.sB[pos] = make_float4(w.cy[i], w.cz[i], __uint_as_float((uint32_t)i), 0.0f);
@@ -481,40 +511,29 @@ __device__ bool rotate_frame(float& x, float p[5], float C[15], float ca, float 
   const float kap = m.kfac * p[4];
   const float x2 = x * ca + p[0] * sa;
   const float y2 = -(x * sa) + p[0] * ca;
-  float J[5][5];
-#pragma unroll
-  for (int i = 0; i < 5; ++i)
-#pragma unroll
-    for (int j = 0; j < 5; ++j) J[i][j] = 0.0f;
-  J[0][0] = ca - (s2 / c2) * sa;
-  J[1][0] = -(p[3] / c2) * sa;
-  J[1][1] = 1.0f;
-  J[2][0] = -kap * sa;
-  J[2][2] = ca + sa * (s / c);
-  J[3][3] = 1.0f;
-  J[4][4] = 1.0f;
-  float T[5][5];
-#pragma unroll
-  for (int i = 0; i < 5; ++i)
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-      float acc = 0.0f;
-#pragma unroll
-      for (int k = 0; k < 5; ++k) acc = acc + J[i][k] * C[sym(k, j)];
-      T[i][j] = acc;
-    }
-  float Cn[15];
-#pragma unroll
-  for (int i = 0; i < 5; ++i)
-#pragma unroll
-    for (int j = i; j < 5; ++j) {
-      float acc = 0.0f;
-#pragma unroll
-      for (int k = 0; k < 5; ++k) acc = acc + T[i][k] * J[j][k];
-      Cn[sym(i, j)] = acc;
-    }
-#pragma unroll
-  for (int i = 0; i < 15; ++i) C[i] = Cn[i];
+  // J C J^T, the terms of J that are not 0 or 1 only, in the order of the
+  // full sums (45 operations instead of 400)
+  const float j00 = ca - (s2 / c2) * sa;
+  const float j10 = -(p[3] / c2) * sa;
+  const float j20 = -kap * sa;
+  const float j22 = ca + sa * (s / c);
+  const float T00 = j00 * C[0], T01 = j00 * C[1], T02 = j00 * C[2];
+  const float T10 = j10 * C[0] + C[1], T11 = j10 * C[1] + C[5], T12 = j10 * C[2] + C[6];
+  const float T13 = j10 * C[3] + C[7], T14 = j10 * C[4] + C[8];
+  const float T20 = j20 * C[0] + j22 * C[2], T22 = j20 * C[2] + j22 * C[9];
+  const float T23 = j20 * C[3] + j22 * C[10], T24 = j20 * C[4] + j22 * C[11];
+  C[3] = j00 * C[3];
+  C[4] = j00 * C[4];
+  C[0] = T00 * j00;
+  C[1] = T00 * j10 + T01;
+  C[2] = T00 * j20 + T02 * j22;
+  C[5] = T10 * j10 + T11;
+  C[6] = T10 * j20 + T12 * j22;
+  C[7] = T13;
+  C[8] = T14;
+  C[9] = T20 * j20 + T22 * j22;
+  C[10] = T23;
+  C[11] = T24;
   x = x2;
   p[0] = y2;
   p[2] = s2;
@@ -727,15 +746,22 @@ __global__ __launch_bounds__(64) void k_its_follow(ItsWs w) {
 }
 
 // Vertex fit: one 512-thread workgroup per event.  Thread tid owns tracks
-// tid + k * TBV (k < kVReg) and keeps their lines (point, direction,
+// tid + k * TBV (k < kVReg) and keeps their lines (point, direction, inverse
 // variance) and weights in registers for all solves; tracks past kVReg TBV
 // are recomputed from memory in each pass.  Per solve each thread sums its
-// tracks in order, the waves sum their lanes by a fixed butterfly and thread
-// 0 adds the waves in order, so the result does not depend on timing.
+// tracks in order, the lanes of a row of 16 add by a fixed butterfly and
+// every wave adds the rows' sums in one order and solves for itself, so the
+// result does not depend on timing.  Bound by the chain of the solves: one
+// barrier each, exchanges between lanes without LDS inside a row (a wave
+// butterfly through LDS, the waves' sums and the solution by thread 0 with
+// four barriers took 38 us for one event of 60 tracks and 78 for 20 of 3,000,
+// this way 18 and 41; six tracks a thread in registers: with four 16 and 55,
+// with eight, which spill, 22 and 73).
 constexpr int TBV = 512;
-constexpr int kVReg = 4;
+constexpr int kVReg = 6;
+constexpr int kVRows = TBV / 16;   // rows of 16 lanes
 
-struct VLine { double P[3], d[3], s2; };
+struct VLine { double P[3], d[3], is2; };
 
 __device__ __forceinline__ VLine its_line(const ItsTab* tb, const tpcca_its_tracks& o, int64_t t) {
   VLine L;
@@ -746,13 +772,13 @@ __device__ __forceinline__ VLine its_line(const ItsTab* tb, const tpcca_its_trac
   const double cc = sqrt(1.0 - sn * sn), nn = sqrt(1.0 + tt * tt);
   L.P[0] = -(yy * sa); L.P[1] = yy * ca; L.P[2] = zz;
   L.d[0] = (cc * ca - sn * sa) / nn; L.d[1] = (cc * sa + sn * ca) / nn; L.d[2] = tt / nn;
-  L.s2 = 0.5 * ((double)o.in_cov[t * 15 + 0] + (double)o.in_cov[t * 15 + 5]);
+  L.is2 = 1.0 / (0.5 * ((double)o.in_cov[t * 15 + 0] + (double)o.in_cov[t * 15 + 5]));
   return L;
 }
 
 // A[0..5] (xx, xy, xz, yy, yz, zz) and b[0..2] += the track's weighted terms
 __device__ __forceinline__ void vfit_acc(const VLine& L, double wgt, double acc[9]) {
-  const double f = wgt / L.s2;
+  const double f = wgt * L.is2;
   double M[3][3];
 #pragma unroll
   for (int r = 0; r < 3; ++r)
@@ -764,52 +790,58 @@ __device__ __forceinline__ void vfit_acc(const VLine& L, double wgt, double acc[
   for (int r = 0; r < 3; ++r) acc[6 + r] += f * (M[r][0] * L.P[0] + M[r][1] * L.P[1] + M[r][2] * L.P[2]);
 }
 
-__device__ __forceinline__ double bisquare(const VLine& L, const double V[3], double c) {
+__device__ __forceinline__ double bisquare(const VLine& L, const double V[3], double ic2) {
   const double u0 = V[0] - L.P[0], u1 = V[1] - L.P[1], u2 = V[2] - L.P[2];
   const double pr = u0 * L.d[0] + u1 * L.d[1] + u2 * L.d[2];
   const double e0 = u0 - pr * L.d[0], e1 = u1 - pr * L.d[1], e2 = u2 - pr * L.d[2];
-  const double D = sqrt((e0 * e0 + e1 * e1 + e2 * e2) / L.s2) / c;
-  return D < 1.0 ? (1.0 - D * D) * (1.0 - D * D) : 0.0;
+  const double D2 = (e0 * e0 + e1 * e1 + e2 * e2) * L.is2 * ic2;
+  return D2 < 1.0 ? (1.0 - D2) * (1.0 - D2) : 0.0;
 }
 
-__device__ __forceinline__ double shfl_xor_d(double v, int m) {
+template <int kCtrl>
+__device__ __forceinline__ double dpp_d(double v) {
   const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)(u & 0xFFFFFFFFull), m, 64);
-  const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(u >> 32), m, 64);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, kCtrl, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), kCtrl, 0xF, 0xF, true);
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Sums of n values over the workgroup, returned to every thread (s: LDS of
-// n * TBV / 64 doubles, out: LDS of n doubles).
+__device__ __forceinline__ double lane_d(double v, int lane) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Sums of N <= 16 values over the workgroup, returned to every thread.  s: LDS
+// of 16 x (kVRows + 1) doubles that the last but one sum may still use (two
+// areas in turn, so that one barrier is enough).
 template <int N>
-__device__ __forceinline__ void vfit_sum(double v[N], double* s, double* out) {
+__device__ __forceinline__ void vfit_sum(double v[N], double (*s)[kVRows + 1]) {
+  const int row = threadIdx.x >> 4, l = threadIdx.x & 63;
 #pragma unroll
-  for (int m = 1; m < 64; m <<= 1)
+  for (int j = 0; j < N; ++j) {
+    v[j] += dpp_d<0xB1>(v[j]);    // lane ^ 1
+    v[j] += dpp_d<0x4E>(v[j]);    // lane ^ 2
+    v[j] += dpp_d<0x141>(v[j]);   // the other four of eight
+    v[j] += dpp_d<0x140>(v[j]);   // the other eight of 16
+  }
+  if ((threadIdx.x & 15) == 0)
 #pragma unroll
-    for (int j = 0; j < N; ++j) v[j] += shfl_xor_d(v[j], m);
-  const int wv = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-#pragma unroll
-    for (int j = 0; j < N; ++j) s[j * (TBV / 64) + wv] = v[j];
+    for (int j = 0; j < N; ++j) s[j][row] = v[j];
   __syncthreads();
-  if (threadIdx.x == 0)
+  // lane l: a quarter of the rows of value l % 16, then the quarters
+  const double* q = s[(l & 15) < N ? (l & 15) : 0] + (l >> 4) * (kVRows / 4);
+  double a = 0.0;
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-      double a = 0.0;
-      for (int q = 0; q < TBV / 64; ++q) a += s[j * (TBV / 64) + q];
-      out[j] = a;
-    }
-  __syncthreads();
+  for (int r = 0; r < kVRows / 4; ++r) a += q[r];
 #pragma unroll
-  for (int j = 0; j < N; ++j) v[j] = out[j];
-  __syncthreads();   // (s and out are reused by the next sum)
+  for (int j = 0; j < N; ++j)
+    v[j] = (lane_d(a, j) + lane_d(a, 16 + j)) + (lane_d(a, 32 + j) + lane_d(a, 48 + j));
 }
 
 __global__ __launch_bounds__(TBV) void k_its_vfit(ItsWs w) {
-  __shared__ double s[9 * (TBV / 64)];
-  __shared__ double out[9];
-  __shared__ double V[3];
-  __shared__ int good;
+  __shared__ double s[2][16][kVRows + 1];
   const int e = blockIdx.x;
   const int tid = threadIdx.x;
   const tpcca_its_tracks& o = w.out[e];
@@ -833,58 +865,51 @@ __global__ __launch_bounds__(TBV) void k_its_vfit(ItsWs w) {
     vw[t] = u ? 1.0 : 0.0;
     c1[0] += u ? 1.0 : 0.0;
   }
-  vfit_sum<1>(c1, s, out);
-  if (tid == 0) { good = c1[0] >= 2.0 ? 1 : 0; V[0] = V[1] = V[2] = 0.0; }
-  __syncthreads();
-  double nused = 0.0, sumw = 0.0;
-  for (int it = 0; it < w.P.fit_iters && good; ++it) {
+  int par = 0;
+  vfit_sum<1>(c1, s[par]);
+  bool good = c1[0] >= 2.0;
+  double V[3] = {0.0, 0.0, 0.0}, nw[2] = {0.0, 0.0};
+  const double ic2 = 1.0 / ((double)w.P.tukey_c * (double)w.P.tukey_c);
+  for (int it = 0; it < w.P.fit_iters && good; ++it) {   // (uniform)
     double acc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < kVReg; ++k)
       if (use[k]) vfit_acc(L[k], wr[k], acc);
     for (int64_t t = tid + (int64_t)kVReg * TBV; t < T; t += TBV)
       if (o.ok[t] && o.in_ok[t]) vfit_acc(its_line(tb, o, t), vw[t], acc);
-    vfit_sum<9>(acc, s, out);
-    if (tid == 0) {
-      const double a00 = acc[0], a01 = acc[1], a02 = acc[2], a11 = acc[3], a12 = acc[4], a22 = acc[5];
-      const double b0 = acc[6], b1 = acc[7], b2 = acc[8];
-      const double c00 = a11 * a22 - a12 * a12, c01 = a02 * a12 - a01 * a22, c02 = a01 * a12 - a02 * a11;
-      const double det = a00 * c00 + a01 * c01 + a02 * c02;
-      if (!(fabs(det) > 0.0)) {
-        good = 0;
-      } else {
-        const double c11 = a00 * a22 - a02 * a02, c12 = a01 * a02 - a00 * a12, c22 = a00 * a11 - a01 * a01;
-        V[0] = (c00 * b0 + c01 * b1 + c02 * b2) / det;
-        V[1] = (c01 * b0 + c11 * b1 + c12 * b2) / det;
-        V[2] = (c02 * b0 + c12 * b1 + c22 * b2) / det;
-      }
-    }
-    __syncthreads();
-    if (!good) break;
-    const double Vl[3] = {V[0], V[1], V[2]};
-    double nw[2] = {0.0, 0.0};
+    par ^= 1;
+    vfit_sum<9>(acc, s[par]);
+    const double a00 = acc[0], a01 = acc[1], a02 = acc[2], a11 = acc[3], a12 = acc[4], a22 = acc[5];
+    const double b0 = acc[6], b1 = acc[7], b2 = acc[8];
+    const double c00 = a11 * a22 - a12 * a12, c01 = a02 * a12 - a01 * a22, c02 = a01 * a12 - a02 * a11;
+    const double det = a00 * c00 + a01 * c01 + a02 * c02;
+    if (!(fabs(det) > 0.0)) { good = false; break; }
+    const double c11 = a00 * a22 - a02 * a02, c12 = a01 * a02 - a00 * a12, c22 = a00 * a11 - a01 * a01;
+    V[0] = (c00 * b0 + c01 * b1 + c02 * b2) / det;
+    V[1] = (c01 * b0 + c11 * b1 + c12 * b2) / det;
+    V[2] = (c02 * b0 + c12 * b1 + c22 * b2) / det;
+    nw[0] = nw[1] = 0.0;
 #pragma unroll
     for (int k = 0; k < kVReg; ++k)
       if (use[k]) {
-        wr[k] = bisquare(L[k], Vl, (double)w.P.tukey_c);
+        wr[k] = bisquare(L[k], V, ic2);
         nw[0] += wr[k] > 0.0 ? 1.0 : 0.0;
         nw[1] += wr[k];
       }
     for (int64_t t = tid + (int64_t)kVReg * TBV; t < T; t += TBV)
       if (o.ok[t] && o.in_ok[t]) {
-        const double wt = bisquare(its_line(tb, o, t), Vl, (double)w.P.tukey_c);
+        const double wt = bisquare(its_line(tb, o, t), V, ic2);
         vw[t] = wt;
         nw[0] += wt > 0.0 ? 1.0 : 0.0;
         nw[1] += wt;
       }
-    vfit_sum<2>(nw, s, out);
-    nused = nw[0];
-    sumw = nw[1];
   }
+  // tracks used and sum of weights of the last solve
+  vfit_sum<2>(nw, s[par ^ 1]);
   if (tid == 0) {
     double* r = w.vres + e * 8;
     r[0] = V[0]; r[1] = V[1]; r[2] = V[2];
-    r[3] = sumw; r[4] = nused; r[5] = good ? 1.0 : 0.0;
+    r[3] = nw[1]; r[4] = nw[0]; r[5] = good ? 1.0 : 0.0;
   }
 }
 
@@ -895,14 +920,13 @@ hipError_t run_its(const ItsWs& w, hipStream_t st) {
   const int64_t ns = (int64_t)w.E * kPerEv;
   const int64_t ninit = std::max<int64_t>(std::max<int64_t>(w.n, (int64_t)w.E * w.nbins), std::max<int64_t>(ns + 1, 4 * w.E));
   k_its_init<<<grid_for(ninit), TB, 0, st>>>(w);
-  k_its_gather<<<g, TB, 0, st>>>(w);
+  k_its_gather<<<grid_for((w.n + kPerThr - 1) / kPerThr), TB, 0, st>>>(w);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   e = scan_exclusive_u32(w.scnt, w.scnt, ns, w.part, st);
   if (e != hipSuccess) return e;
   e = scan_exclusive_u32(w.l0f, w.l0f, w.n, w.part, st);
   if (e != hipSuccess) return e;
-  k_its_cursors<<<grid_for(ns), TB, 0, st>>>(w);
   k_its_fill<<<g, TB, 0, st>>>(w);
   const unsigned gg = grid_for(w.n * kGrp);   // (kGrp lanes per layer-0 cluster)
   k_its_vpairs<<<gg, TB, 0, st>>>(w);
@@ -1047,7 +1071,7 @@ int tpcca_its_track_batch(tpcca_its_ctx* c, int32_t E, const tpcca_its_clusters*
   const size_t o_up = take(up_bytes), o_res = take(res_bytes);
   const size_t o_cx = take(4 * nn), o_cy = take(4 * nn), o_cz = take(4 * nn), o_cl = take(nn), o_ck = take(2 * nn);
   const size_t o_cev = take(4 * nn), o_X = take(4 * nn), o_Y = take(4 * nn), o_R = take(4 * nn);
-  const size_t o_scnt = take(4 * (ns + 1)), o_scur = take(4 * ns), o_slist = take(4 * nn);
+  const size_t o_scnt = take(4 * (ns + 1)), o_rank = take(4 * nn), o_slist = take(4 * nn);
   const size_t o_sA = take(16 * nn), o_sB = take(16 * nn), o_l0f = take(4 * (nn + 1)), o_l0l = take(4 * nn);
   const size_t o_hist = take(4 * (int64_t)E * nbins);
   const size_t o_b0 = take(8 * nn), o_b1 = take(8 * nn), o_tf = take(4 * (nn + 1));
@@ -1110,7 +1134,7 @@ int tpcca_its_track_batch(tpcca_its_ctx* c, int32_t E, const tpcca_its_clusters*
   w.cx = (float*)(b + o_cx); w.cy = (float*)(b + o_cy); w.cz = (float*)(b + o_cz);
   w.cl = (int8_t*)(b + o_cl); w.ck = (int16_t*)(b + o_ck); w.cev = (int32_t*)(b + o_cev);
   w.cX = (float*)(b + o_X); w.cY = (float*)(b + o_Y); w.cR = (float*)(b + o_R);
-  w.err = (uint32_t*)(b + o_res + r_err); w.scnt = (uint32_t*)(b + o_scnt); w.scur = (uint32_t*)(b + o_scur);
+  w.err = (uint32_t*)(b + o_res + r_err); w.scnt = (uint32_t*)(b + o_scnt); w.rank = (uint32_t*)(b + o_rank);
   w.slist = (uint32_t*)(b + o_slist); w.sA = (float4*)(b + o_sA); w.sB = (float4*)(b + o_sB);
   w.l0f = (uint32_t*)(b + o_l0f); w.l0list = (uint32_t*)(b + o_l0l);
   w.hist = (uint32_t*)(b + o_hist); w.vsum = (unsigned long long*)(b + o_res + r_vsum);

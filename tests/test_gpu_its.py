@@ -157,3 +157,17 @@ def test_its_edges(its_tracker):
     b = its_tracker.track(x, y, z, lay, stv)
     m = (a.ok * a.in_ok).bool()
     assert torch.equal(a.ok, b.ok) and torch.equal(a.in_p[m], b.in_p[m]) and a.vertex == b.vertex
+
+
+@pytest.mark.parametrize("primaries", [3, 400, 5200])
+def test_its_event_sizes_around_the_fit_registers(its_tracker, orc, primaries):
+    """Events whose tracks the vertex fit keeps in registers (up to 3,072) or
+    partly reads again, alone and behind other events (whose clusters share
+    the gather's workgroups), equal the oracle."""
+    ev = synth.make_its_event(seed=81, n_primaries=primaries)
+    ref = orc.its(ev)
+    check_vs_oracle(its_tracker.track(*dev(ev), hist=True), ref)
+    small = synth.make_its_config("ITS-pp")
+    got = its_tracker.track_batch([dev(small), dev(ev), dev(small), dev(ev)], hist=True)
+    check_vs_oracle(got[1], ref)
+    check_vs_oracle(got[3], ref)
