@@ -795,7 +795,8 @@ __device__ __forceinline__ double bisquare(const VLine& L, const double V[3], do
   const double pr = u0 * L.d[0] + u1 * L.d[1] + u2 * L.d[2];
   const double e0 = u0 - pr * L.d[0], e1 = u1 - pr * L.d[1], e2 = u2 - pr * L.d[2];
   const double D2 = (e0 * e0 + e1 * e1 + e2 * e2) * L.is2 * ic2;
-  return D2 < 1.0 ? (1.0 - D2) * (1.0 - D2) : 0.0;
+  // (a negative variance has no distance: weight 0, as its root would give)
+  return D2 >= 0.0 && D2 < 1.0 ? (1.0 - D2) * (1.0 - D2) : 0.0;
 }
 
 template <int kCtrl>

@@ -2215,9 +2215,9 @@ __global__ __launch_bounds__(TB, 4) void k_tracklets(Ws w) {
 // ----------------------------------------------------------- a6: selection
 // Ownership by bands of kBandRows pad rows of one (event, sector): tracklets
 // of different sectors never share a cluster, so the workgroup of a band
-// scans its sector's tracklets (four lanes per tracklet, one per row) and
+// scans its sector's tracklets (a thread per tracklet and band) and
 // takes the key maximum of each of the band's clusters with LDS atomics,
-// then writes the band's owners out in order.  A band with more than
+// then writes the mask of each tracklet's owned rows.  A band with more than
 // kBandCap clusters uses global atomics on the (zeroed) owner array instead.
 constexpr int kBandRows = 8;
 constexpr int kBandCap = 6144;
