@@ -171,3 +171,26 @@ def test_its_event_sizes_around_the_fit_registers(its_tracker, orc, primaries):
     got = its_tracker.track_batch([dev(small), dev(ev), dev(small), dev(ev)], hist=True)
     check_vs_oracle(got[1], ref)
     check_vs_oracle(got[3], ref)
+
+
+@pytest.mark.parametrize("half_range,bin_width", [(0.05, 0.1), (20.0, 0.1), (20.0, 40.0 / 4096)])
+def test_its_vertexer_histogram_sizes(orc, half_range, bin_width):
+    """One bin, the default 400 and the largest number of bins (4,096): counts,
+    peak and mean z per event equal the oracle's, alone and in a batch."""
+    from paper_1712_09434_amd.its import ItsTracker
+    p, q = ItsTracker.default_params(), orc.its_default_params()
+    p.vtx_range = q.vtx_range = half_range
+    p.vtx_bin = q.vtx_bin = bin_width
+    trk = ItsTracker(synth.default_its_geometry(), p)
+    try:
+        evs = [synth.make_its_config("ITS-pp"), synth.make_its_event(seed=91, n_primaries=300)]
+        refs = [orc.its(e, q) for e in evs]
+        outs = trk.track_batch([dev(evs[i]) for i in (0, 1, 0)], hist=True)
+        for out, ref in zip(outs + [trk.track(*dev(evs[1]), hist=True)], [refs[i] for i in (0, 1, 0, 1)]):
+            np.testing.assert_array_equal(out.hist.cpu().numpy().astype(np.int64), ref["hist"])
+            assert (out.n_pairs, out.peak, out.vz_ok) == (ref["n_pairs"], ref["peak"], ref["vz_ok"])
+            assert np.float32(out.vz) == np.float32(ref["vz"]) and out.tl0.shape[0] == len(ref["tl0"])
+            if len(ref["tl0"]):   # (none where the vertices lie outside the range)
+                check_vs_oracle(out, ref)
+    finally:
+        trk.close()
