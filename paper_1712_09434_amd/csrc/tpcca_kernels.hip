@@ -1527,6 +1527,9 @@ __global__ __launch_bounds__(TB) void k_links(Ws w, uint32_t cap) {
 // Keep a link only if reciprocated (from the raw arrays).  Start hit: kept up
 // link, no kept down link.  Seed: start hit whose chain reaches
 // min_seed_hits clusters.  Optional taps map positions to cluster ids.
+// Invalid clusters have no row unit and so no position: the positions behind
+// the last row unit hold what earlier calls left and are flagged only (the
+// call reports the error at its end).
 // Bound by memory: the up link goes into the record that the rows have
 // written (4 bytes of its 16; records written here as well took 55 us
 // instead of 43 on 3.8 M clusters, a link array of its own 36 but 15 more in
@@ -1535,7 +1538,7 @@ __global__ __launch_bounds__(TB) void k_clean(Ws w) {
   __shared__ uint32_t s_cnt[2][TB / 64];
   const int64_t p = (int64_t)blockIdx.x * TB + threadIdx.x;
   bool start = false, seed = false;
-  if (p < w.N) {
+  if (p < (int64_t)w.ru_off[w.RU]) {
     // both links, then both reciprocity gathers together
     // (a missing link reads the cluster's own entry, which is not used)
     const int32_t u = w.up[p], d = w.dn[p];
@@ -1566,6 +1569,8 @@ __global__ __launch_bounds__(TB) void k_clean(Ws w) {
       if (O.dbg_cup) O.dbg_cup[id] = cu >= 0 ? (int32_t)w.cid[cu] : -1;
       if (O.dbg_cdn) O.dbg_cdn[id] = cd >= 0 ? (int32_t)w.cid[cd] : -1;
     }
+  } else if (p < w.N) {
+    w.flag[p] = 0;
   }
   const uint64_t bs = __ballot(start), bq = __ballot(seed);
   if (lane_id() == 0) { s_cnt[0][threadIdx.x >> 6] = (uint32_t)__popcll(bs); s_cnt[1][threadIdx.x >> 6] = (uint32_t)__popcll(bq); }

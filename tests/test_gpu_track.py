@@ -575,3 +575,33 @@ def test_regrouped_seeds_with_any_grid(tracker, orc, grid):
     for b in batch:
         for k in ("hit_off", "hit_id", "p", "cov", "chi2", "k_prior"):
             assert torch.equal(getattr(b, k), getattr(batch[0], k)), k
+
+
+@pytest.mark.parametrize("events", [1, 4])
+def test_many_invalid_clusters_after_other_sizes(tracker, events):
+    """Invalid clusters get no position: the workspace behind the valid ones
+    holds what calls of other sizes left there, and nothing may follow it.
+    Events of which half or all clusters are invalid, alone and in a batch
+    (size classes by list), taps on and off, are refused, and the valid event
+    gives the same tracks as before."""
+    from paper_1712_09434_amd import _abi as A
+    from paper_1712_09434_amd import TpccaError
+    ev = synth.make_config("C1")
+    base = to_dev(ev)
+    first = tracker.track(*base)
+    other = to_dev(synth.make_event(seed=91, n_primaries=900, noise=0.05))
+    rng = np.random.default_rng(92)
+    for frac in (0.5, 1.0):
+        bad = torch.from_numpy(np.nonzero(rng.random(ev.n) < frac)[0]).to("cuda:0")
+        for field, value in ((0, float("inf")), (2, float("nan")), (3, -1), (3, 159), (4, 36)):
+            tracker.track(*other)   # another layout of the workspace, full of its own links and floats
+            event = [t.clone() for t in base]
+            event[field][bad] = value
+            for taps in (False, True):
+                print(f"[gpu] {frac} of {ev.n} clusters invalid, field {field}, taps {taps}", flush=True)
+                with pytest.raises(TpccaError) as e:
+                    tracker.track_batch([base] * (events - 1) + [tuple(event)], taps=taps)
+                assert e.value.code == A.TPCCA_E_INVALID
+            again = tracker.track(*base)
+            for k in ("hit_off", "hit_id", "p", "cov", "chi2"):
+                assert torch.equal(getattr(again, k), getattr(first, k)), (frac, field, k)
