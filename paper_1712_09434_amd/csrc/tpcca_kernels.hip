@@ -969,7 +969,10 @@ __global__ __launch_bounds__(TB) void k_rows(Ws w) {
 
 // Cell rectangle [iz0, iz1] x [iy0, iy1] covering |y - yq| <= wy, |z - zq| <= wz
 // (the margin absorbs the rounding of the bounds; the exact test is done per
-// candidate).
+// candidate).  The bounds are cell coordinates of positions, by the same
+// monotone function as the entries': wherever the query lies and however
+// small the cells are beside the window, an entry between two positions has
+// its cell between theirs.
 struct CellBox { uint32_t iz0, iz1, iy0, iy1; };
 __device__ __forceinline__ CellBox cell_box(const GridParams& G, float yq, float zq, float wy, float wz) {
   const float m = 1e-3f;
@@ -1047,18 +1050,12 @@ struct CandList {
 // Window scan of one row's box: indices (into D4) of the entries within the
 // windows, the first kMax of them to out; returns their count.  Two z rows
 // of the box at a time are taken as one list, so that a lane waits for LDS
-// once for their bounds and once per four entries.  The box is taken in
-// cells, with 2e-3 cells for the rounding there (coordinates of at most 4097
-// cells).
+// once for their bounds and once per four entries.
 template <int kMax, class Idx>
 __device__ __forceinline__ int collect(const GridParams& G, const float4* D4, const uint16_t* Dc, float yi, float zi,
                                        float WY, float WZ, Idx* out) {
-  const uint32_t nz = G.nz(), ny = G.ny();
-  const float fz = (float)(nz - 1u), fy = (float)(ny - 1u);
-  const float tz = (zi - G.z0) * G.inv_bz, hz = fmaf(WZ, G.inv_bz, 2e-3f);
-  const float ty = (yi - G.y0) * G.inv_by, hy = fmaf(WY, G.inv_by, 2e-3f);
-  const uint32_t iz0 = (uint32_t)fminf(fmaxf(tz - hz, 0.0f), fz), iz1 = (uint32_t)fminf(fmaxf(tz + hz, 0.0f), fz);
-  const uint32_t iy0 = (uint32_t)fminf(fmaxf(ty - hy, 0.0f), fy), iy1 = (uint32_t)fminf(fmaxf(ty + hy, 0.0f), fy) + 1u;
+  const CellBox b = cell_box(G, yi, zi, WY, WZ);
+  const uint32_t ny = G.ny(), iz0 = b.iz0, iz1 = b.iz1, iy0 = b.iy0, iy1 = b.iy1 + 1u;
   int n = 0;
   for (uint32_t iz = iz0; iz <= iz1; iz += 2) {
     const uint16_t* c0 = Dc + iz * ny;

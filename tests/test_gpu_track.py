@@ -605,3 +605,58 @@ def test_many_invalid_clusters_after_other_sizes(tracker, events):
             again = tracker.track(*base)
             for k in ("hit_off", "hit_id", "p", "cov", "chi2"):
                 assert torch.equal(getattr(again, k), getattr(first, k)), (frac, field, k)
+
+
+def _window_edge_event(seed, win, extent, axis):
+    """One sector of row triples: a middle row of 200 clusters, on the row
+    below 200 or 400 clusters within `extent` cm of each other, and as many
+    above, the two clumps two windows apart along `axis` (1: y, 2: z).  The
+    middle clusters lie exactly a window from one of the last clusters of the
+    lower clump, so a few clusters of each clump are candidates, the outermost
+    of them at the very edge."""
+    import dataclasses
+    rng = np.random.default_rng(seed)
+    g = synth.default_geometry()
+    f, w = np.float32, np.float32(win)
+    rows, along, across = [], [], []
+
+    def add(r, a):
+        rows.append(np.full(len(a), r, np.int16))
+        along.append(a.astype(f))
+        across.append(rng.uniform(0.0, extent, len(a)).astype(f))
+
+    for i, r in enumerate(range(1, 157, 4)):
+        n = 200 if i % 2 == 0 else 400
+        at = f(rng.uniform(-0.05, 0.05))
+        low = np.sort((at + rng.uniform(0.0, extent, n)).astype(f))
+        high = (low[-12] + 2 * w + rng.uniform(0.0, extent, n)).astype(f)
+        add(r - 1, low)
+        add(r, low[rng.integers(n - 14, n, 200)] + w)
+        add(r + 1, high)
+    rows, along, across = (np.concatenate(a) for a in (rows, along, across))
+    perm = rng.permutation(len(rows))
+    rows, along, across = rows[perm], along[perm], across[perm]
+    y, z = (along, across) if axis == 1 else (across, along)
+    x = np.asarray(g.row_x, f)[rows]
+    n = len(rows)
+    ev = synth.make_event(seed=1, n_primaries=0)
+    return dataclasses.replace(ev, x=x, y=y, z=z, row=rows, sector=np.zeros(n, np.uint8), x64=x.astype(np.float64),
+                               y64=y.astype(np.float64), z64=z.astype(np.float64),
+                               truth_track=np.full(n, -1, np.int32), truth_double=np.zeros(n, bool))
+
+
+@pytest.mark.parametrize("axis,win", [(1, 2.0), (2, 2.2)])
+@pytest.mark.parametrize("extent", [1e-3, 1e-4])
+def test_links_at_the_window_edge_of_clumped_rows(tracker, orc, axis, win, extent):
+    """Rows whose clusters lie within micrometres have cells thousands of
+    times smaller than the link window, so a window's bounds in cells carry
+    the rounding of coordinates far outside the grid: the candidates exactly
+    at the window's edge are found all the same, in rows of both link kernels
+    and in a batch."""
+    ev = _window_edge_event(95 + axis, win, extent, axis)
+    print(f"[gpu] window edge n={ev.n}", flush=True)
+    ref = orc.track(ev, precision=32)
+    mid = ev.row % 4 == 1
+    assert (ref["up"][mid] >= 0).mean() > 0.5
+    for out in [tracker.track(*to_dev(ev), taps=True)] + tracker.track_batch([to_dev(ev)] * 3, taps=True):
+        compare(ev, out, None, ref)
