@@ -456,14 +456,20 @@ __global__ void k_mrg_total(const uint32_t* __restrict__ v, int64_t T, uint32_t*
 }
 
 // One wave per segment: its hit ids copied to their place in the output
-// (the chain's hits, innermost segment first).
+// (the chain's hits, innermost segment first).  The hits of chains that will
+// be refitted are checked here; a segment of its own is copied as it is.
 __global__ __launch_bounds__(TB) void k_mrg_hits(MergeWs w) {
   const int64_t c = (int64_t)blockIdx.x * (TB / 64) + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (c >= w.T || w.err[0] != 0u) return;
   const uint32_t h = w.hemit[w.head[c]] + w.hpos[c];
   const int32_t b0 = w.hit_off[c], nh = w.hit_off[c + 1] - b0;
-  for (int32_t k = lane; k < nh; k += 64) w.o_hit_id[h + (uint32_t)k] = w.hit_id[b0 + k];
+  const bool refit = w.nseg[w.head[c]] > 1u;
+  for (int32_t k = lane; k < nh; k += 64) {
+    const uint32_t id = w.hit_id[b0 + k];
+    if (refit && (int64_t)id >= w.NC) atomicOr(&w.err[0], 2u);
+    w.o_hit_id[h + (uint32_t)k] = id;
+  }
 }
 
 // Merged refit of a listed chain, from its outermost hit inward over the
@@ -476,7 +482,7 @@ __global__ __launch_bounds__(TB) void k_mrg_hits(MergeWs w) {
 // so a lane crossing a boundary does not stop its wave for dependent loads.
 __global__ __launch_bounds__(64) void k_mrg_refit(MergeWs w) {
   const int64_t q = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (q >= (int64_t)w.err[3]) return;
+  if (q >= (int64_t)w.err[3] || w.err[0] != 0u) return;
   const int32_t i = (int32_t)w.rlist[q];
   const uint32_t* ids = w.o_hit_id + w.hemit[i];
   int32_t c = i;

@@ -160,3 +160,34 @@ def test_merge_edges(tracker):
                                       ("sector", "x_ref", "p", "cov", "chi2", "ndf", "k_prior", "hit_off", "hit_id")})
     with pytest.raises(TpccaError):
         tracker.merge(hseg, tuple(t.cpu() for t in cl))
+
+
+def test_merge_rejects_bad_hits_inside_a_chain(tracker):
+    """Every hit of a chain that is refitted must index the clusters, also
+    between the first and the last of a segment; a segment that joins no
+    chain is copied as it is."""
+    import dataclasses
+    from paper_1712_09434_amd import _abi as A
+    from paper_1712_09434_amd import TpccaError
+    ev = synth.make_event(seed=6, n_primaries=300, noise=0.05)
+    cl = to_dev(ev)
+    seg = tracker.track(*cl)
+    good, links = tracker.merge(seg, cl, links=True)
+    lk, off = links.cpu().numpy(), seg.hit_off.cpu().numpy()
+    inner = np.nonzero(lk >= 0)[0]
+    single = np.setdiff1d(np.arange(len(lk)), np.concatenate([inner, lk[inner]]))
+    assert len(inner) and len(single)
+    for s, value in ((inner[0], ev.n), (lk[inner[-1]], -1), (inner[len(inner) // 2], 0x7FFFFFFF)):
+        ids = seg.hit_id.clone()
+        ids[int(off[s] + off[s + 1]) // 2] = value
+        print(f"[gpu] segment {s}: hit id {value} of {ev.n} clusters", flush=True)
+        with pytest.raises(TpccaError) as e:
+            tracker.merge(dataclasses.replace(seg, hit_id=ids), cl)
+        assert e.value.code == A.TPCCA_E_INVALID
+    ids = seg.hit_id.clone()
+    ids[int(off[single[0]] + off[single[0] + 1]) // 2] = -1
+    copied = tracker.merge(dataclasses.replace(seg, hit_id=ids), cl)
+    assert int((copied.hit_id != good.hit_id).sum()) == 1 and int((copied.hit_id == -1).sum()) == 1
+    again = tracker.merge(seg, cl)
+    for k in ("hit_off", "hit_id", "p", "cov", "chi2", "sector"):
+        assert torch.equal(getattr(again, k), getattr(good, k)), k
