@@ -472,7 +472,10 @@ __device__ __forceinline__ uint32_t cell_of(const GridParams& G, float y, float 
 // degenerate or n < 4).  The grid only bounds what a search visits, so
 // hardware reciprocals and roots (1 ulp) do; nz ny <= cap holds as a
 // quotient of integers up to kMaxCells that is not an integer lies further
-// than a few ulp below the next one.
+// than a few ulp below the next one.  The reciprocal cell sizes stay finite
+// where the box is subnormal (its entries then share a cell): the search
+// adds and subtracts products with them, which must not be infinite.
+constexpr float kMaxInv = 0x1p60f;
 __device__ __forceinline__ GridParams make_grid(uint32_t n, uint32_t cbase, uint32_t off, float ymin, float ymax,
                                                 float zmin, float zmax) {
   const uint32_t cap = grid_cells(n);
@@ -488,8 +491,8 @@ __device__ __forceinline__ GridParams make_grid(uint32_t n, uint32_t cbase, uint
   GridParams G;
   G.cell_base = cbase; G.base = off; G.dims = GridParams::pack((uint32_t)nz, (uint32_t)ny); G.pad = 0u;
   G.z0 = zmin; G.y0 = ymin;
-  G.inv_bz = dz > 0.0f ? nz * __builtin_amdgcn_rcpf(dz) : 0.0f;
-  G.inv_by = dy > 0.0f ? ny * __builtin_amdgcn_rcpf(dy) : 0.0f;
+  G.inv_bz = dz > 0.0f ? fminf(nz * __builtin_amdgcn_rcpf(dz), kMaxInv) : 0.0f;
+  G.inv_by = dy > 0.0f ? fminf(ny * __builtin_amdgcn_rcpf(dy), kMaxInv) : 0.0f;
   return G;
 }
 

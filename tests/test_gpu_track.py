@@ -660,3 +660,45 @@ def test_links_at_the_window_edge_of_clumped_rows(tracker, orc, axis, win, exten
     assert (ref["up"][mid] >= 0).mean() > 0.5
     for out in [tracker.track(*to_dev(ev), taps=True)] + tracker.track_batch([to_dev(ev)] * 3, taps=True):
         compare(ev, out, None, ref)
+
+
+def _subnormal_event():
+    """One sector of nine straight tracks in the plane z = 0, the rows 80 to 82
+    left out, whose z is 0 up to there and the smallest steps above it (10^-40
+    cm) beyond, the other way round or alternating: row grids whose reciprocal
+    cell size overflows."""
+    import dataclasses
+    g = synth.default_geometry()
+    rows = np.array([r for r in range(g.n_rows) if not 80 <= r <= 82])
+    slope = np.linspace(-0.13, 0.13, 9)
+    x = np.asarray(g.row_x, np.float32)[rows]
+    tiny = np.float32(1e-40)
+    y = np.concatenate([(s * x.astype(np.float64)).astype(np.float32) for s in slope])
+    z = np.concatenate([np.where([rows < 80, rows > 80, rows % 2 == 0][k % 3], np.float32(0), tiny)
+                        for k in range(9)]).astype(np.float32)
+    n = len(y)
+    rows, x = np.tile(rows, 9).astype(np.int16), np.tile(x, 9)
+    ev = synth.make_event(seed=1, n_primaries=0)
+    return dataclasses.replace(ev, x=x, y=y, z=z, row=rows, sector=np.zeros(n, np.uint8), x64=x.astype(np.float64),
+                               y64=y.astype(np.float64), z64=z.astype(np.float64),
+                               truth_track=np.repeat(np.arange(9), n // 9).astype(np.int32),
+                               truth_double=np.zeros(n, bool))
+
+
+@pytest.mark.parametrize("copies", [1, 1830])
+def test_rows_of_subnormal_extent(tracker, orc, copies):
+    """Clusters of a row that differ by subnormal steps only are found on both
+    sides of a gap, by groups of lanes per seed and by single lanes."""
+    ev = _subnormal_event()
+    ref = orc.track(ev, precision=32)
+    assert len(ref["x_ref"]) == 9 and (np.diff(ref["hit_off"]) == 156).all()
+    t = to_dev(ev)
+    out = tracker.track(*t, taps=True)
+    tl = tracker.debug_tracklets()
+    seeds = len(tl["seed_start"])
+    compare(ev, out, tl, ref)
+    if copies > 1:
+        assert seeds * copies > 32768
+        print(f"[gpu] {copies} copies of {seeds} seeds", flush=True)
+        for b in tracker.track_batch([t] * copies)[::copies // 3]:
+            compare(ev, b, None, ref, check_taps=False)
