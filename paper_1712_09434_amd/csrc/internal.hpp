@@ -114,6 +114,7 @@ struct Ws {
   const float* row_x;   // [R]
   Model m;
   tpcca_params P;
+  float ext_w;          // half width of the row search's window in standard deviations (1.0001 sqrt(chi2_ext))
   float tan_a, z_max;   // acceptance: |y| <= x tan_a, |z| <= z_max
   int tracklet_grid;    // workgroups of the tracklet kernel (0 = automatic)
   int taps;             // 1 if some event of the call asks for link or start-hit taps

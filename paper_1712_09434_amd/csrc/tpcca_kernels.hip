@@ -1664,11 +1664,13 @@ __device__ __forceinline__ Found search_row(const Ws& w, const GridParams& Q, co
   if (__builtin_expect(max(rcp_key(sy2), rcp_key(sz2)) > kRcpKey, 0)) { isy = 1.0f / sy2; isz = 1.0f / sz2; }
   // the window only bounds the cells scanned: the hardware square root
   // (1 ulp) is enough under the 1e-4 relative and 1e-3 cm margins; the
-  // bounds are taken in cells, with 2e-3 cells for the rounding there
-  // (coordinates of at most 4097 cells), so the scanned cells stay a
-  // superset of those of every cluster passing the cut
-  const float wy = 3.0003f * __builtin_amdgcn_sqrtf(sy2) + 1e-3f;
-  const float wz = 3.0003f * __builtin_amdgcn_sqrtf(sz2) + 1e-3f;
+  // bounds are taken in cells, with 2e-3 cells for the rounding inside the
+  // grid (coordinates of at most 4097 cells; of a query further out, by the
+  // window, it is 4e-7 of the window in cells, within the relative margin),
+  // so the scanned cells stay a superset of those of every cluster passing
+  // the cut
+  const float wy = fmaf(w.ext_w, __builtin_amdgcn_sqrtf(sy2), 1e-3f);
+  const float wz = fmaf(w.ext_w, __builtin_amdgcn_sqrtf(sz2), 1e-3f);
   const uint32_t nz = Q.nz(), ny = Q.ny();
   const float fz = (float)(nz - 1u), fy = (float)(ny - 1u);
   const float tz = (p[1] - Q.z0) * Q.inv_bz, hz = fmaf(wz, Q.inv_bz, 2e-3f);

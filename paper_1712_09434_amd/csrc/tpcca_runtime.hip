@@ -467,6 +467,7 @@ int tpcca_track_batch(tpcca_ctx* c, int32_t E, const tpcca_clusters* ev, tpcca_t
   w.row_x = c->row_x_d;
   w.m = make_model(c->bz, c->P);
   w.P = c->P;
+  w.ext_w = 1.0001f * std::sqrt(c->P.chi2_ext);
   w.tan_a = c->tan_a;
   w.z_max = c->z_max;
   w.tracklet_grid = c->tune.tracklet_grid;

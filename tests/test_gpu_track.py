@@ -702,3 +702,57 @@ def test_rows_of_subnormal_extent(tracker, orc, copies):
         print(f"[gpu] {copies} copies of {seeds} seeds", flush=True)
         for b in tracker.track_batch([t] * copies)[::copies // 3]:
             compare(ev, b, None, ref, check_taps=False)
+
+
+def _displaced_event():
+    """One sector of 25 straight tracks whose clusters on four rows lie 1.6 cm
+    aside: further than links reach over.  These rows hold 1,500 other
+    clusters at larger z, so that their cells are smaller than that."""
+    import dataclasses
+    rng = np.random.default_rng(97)
+    g = synth.default_geometry()
+    row_x = np.asarray(g.row_x, np.float32)
+    rows, ys, zs = [], [], []
+    for s in np.linspace(-0.12, 0.12, 25):
+        r = np.arange(g.n_rows)
+        y = s * row_x.astype(np.float64) + np.where(np.isin(r, (30, 60, 90, 120)), 1.6 * np.sign(0.05 - s), 0.0)
+        rows.append(r)
+        ys.append(y + rng.normal(0.0, 0.02, len(r)))
+        zs.append((0.01 + 0.1 * abs(s)) * row_x + rng.normal(0.0, 0.02, len(r)))
+    for r in (30, 60, 90, 120):
+        rows.append(np.full(1500, r))
+        ys.append(rng.uniform(-0.13, 0.13, 1500) * row_x[r])
+        zs.append(rng.uniform(20.0, 40.0, 1500))
+    rows, ys, zs = np.concatenate(rows), np.concatenate(ys), np.concatenate(zs)
+    n = len(rows)
+    ev = synth.make_event(seed=1, n_primaries=0)
+    x, y, z = row_x[rows], ys.astype(np.float32), zs.astype(np.float32)
+    return dataclasses.replace(ev, x=x, y=y, z=z, row=rows.astype(np.int16), sector=np.zeros(n, np.uint8),
+                               x64=x.astype(np.float64), y64=y.astype(np.float64), z64=z.astype(np.float64),
+                               truth_track=np.full(n, -1, np.int32), truth_double=np.zeros(n, bool))
+
+
+@pytest.mark.parametrize("cut", [4.0, 400.0])
+@pytest.mark.parametrize("lanes,copies", [(8, 1), (4, 140), (1, 530)])
+def test_search_windows_follow_the_cut(orc, cut, lanes, copies):
+    """Row searches with other cuts than the default three standard
+    deviations: links, tracklets and tracks equal the oracle with the same
+    parameters, with eight, four and one lane per seed."""
+    from paper_1712_09434_amd import Tracker
+    ev = _displaced_event()
+    trk = Tracker.from_geometry(ev.geom)
+    try:
+        p, q = trk.get_params(), orc.default_params()
+        p.chi2_ext = q.chi2_ext = cut
+        trk.set_params(p)
+        ref = orc.track(ev, precision=32, params=q)
+        seeds = len(ref["seed_start"]) * copies
+        assert lanes == (8 if seeds <= 8192 else 4 if seeds <= 32768 else 1)
+        print(f"[gpu] cut {cut}, {seeds} seeds", flush=True)
+        if copies == 1:
+            out = trk.track(*to_dev(ev), taps=True)
+            compare(ev, out, trk.debug_tracklets(), ref)
+        else:
+            compare(ev, trk.track_batch([to_dev(ev)] * copies)[copies // 2], None, ref, check_taps=False)
+    finally:
+        trk.close()
