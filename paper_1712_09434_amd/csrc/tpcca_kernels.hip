@@ -2169,7 +2169,7 @@ constexpr uint32_t kSeeds8 = 8192, kSeeds4 = 32768;
 __device__ __forceinline__ int tracklet_lanes(uint32_t ns) { return ns <= kSeeds8 ? 8 : ns <= kSeeds4 ? 4 : 1; }
 
 // Reads one word of every 128-byte line of [p, p + bytes), the lines spread
-// over nt threads of which this is thread t.
+// over nt threads of which this is thread t (p and bytes: multiples of 4).
 __device__ __forceinline__ void touch_lines(const void* p, int64_t bytes, int64_t t, int64_t nt) {
   uint32_t acc = 0;
   for (int64_t i = t * 128; i < bytes; i += nt * 128) acc |= *(const uint32_t*)((const char*)p + i);
@@ -2210,7 +2210,9 @@ __global__ __launch_bounds__(TB, 4) void k_tracklets(Ws w) {
     const int64_t nt = ((int64_t)(gridDim.x + kXcd - 1 - x) / kXcd - b0) * TB;
     const int64_t t = ((int64_t)(blockIdx.x / kXcd) - b0) * TB + threadIdx.x;
     touch_lines(w.grid + u0, (int64_t)(u1 - u0) * (int64_t)sizeof(GridParams), t, nt);
-    touch_lines(w.cell_off + k0, (k1 - k0) * 2, t, nt);
+    // (words of two offsets from an even one; the array has an entry more than it needs)
+    const int64_t ka = k0 & ~(int64_t)1;
+    touch_lines(w.cell_off + ka, (k1 - ka + 1) / 2 * 4, t, nt);
     touch_lines(w.gbuf + c0, (c1 - c0) * 16, t, nt);
     return;
   }
