@@ -27,6 +27,15 @@ namespace {
 
 constexpr int TB = 256;
 
+// Ordering of LDS accesses between the lanes of one wave (the wave's LDS
+// operations complete in order; this keeps the compiler from moving accesses
+// across).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ------------------------------------------------------------ dual numbers
 // A value with its derivatives along three directions (d0, d1, d2).  Bit i of
 // M: derivative i may be non-zero; the others are known to be zero, and no
@@ -935,13 +944,11 @@ __global__ __launch_bounds__(TB) void k_cal_partials(CalWs c) {
   };
   fetch(n - 1);
   for (int i0 = n - 1; i0 >= 0; i0 -= kPartLanes) {
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();   // (the last sixteen have been read)
     *(uint4*)(rec + l * kHit) = h;
     *(float4*)(rec + l * kHit + 4) = va;
     *(float4*)(rec + l * kHit + 8) = vb;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
     fetch(i0 - kPartLanes);
     const int m = min(kPartLanes, i0 + 1);
 #pragma unroll 4
@@ -1003,6 +1010,7 @@ __global__ __launch_bounds__(TB) void k_cal_chunks(CalWs c) {
   for (int sb = 0; sb < c.S; sb += kSecGrp) {
     const int ns = min(kSecGrp, c.S - sb);
     for (int q = lane; q < ns * kNPar; q += 64) (&s_acc[wv][0][0])[q] = 0.0;
+    wave_sync();   // (cleared by other lanes than those that add)
     constexpr int kU = 8;   // rows in flight
     for (int u0 = 0; u0 < 64; u0 += kU) {
       float v[kU], v2[kU];
