@@ -127,6 +127,7 @@ class ItsTracker:
         run(results=True): one tpcca_its_track_batch call on it, for repeated
         calls on the same inputs.  The result tensors of the events are slices
         of one array per field."""
+        events = list(events)
         E = len(events)
         if E == 0:
             return lambda results=True: []
