@@ -21,6 +21,12 @@ _FIELDS = {k: (torch.float32 if k in ("chi2", "out_x", "out_p", "out_cov", "in_p
            for k in A.ITS_TRACK_ARRAYS}
 _CLUSTERS_DT = struct_dtype(A.tpcca_its_clusters)
 _TRACKS_DT = struct_dtype(A.tpcca_its_tracks)
+# The tracklets are at most the layer-0 clusters, but counting those waits for
+# the device: calls of up to this many clusters hold an entry per cluster (224
+# bytes, about six times what they need) instead (one small event 313 us with
+# the wait, 283 without).  Beyond, where the wait no longer shows, the
+# layer-0 clusters are counted, so that the surplus stays below 200 MB a call.
+_COUNT_ABOVE = 1 << 20
 
 
 def _check(L, ctx, rc):
@@ -97,9 +103,7 @@ class ItsTracker:
         keep = [t.contiguous() for t in (x, y, z, layer, stave)]
         cl.x, cl.y, cl.z, cl.layer, cl.stave = (_ptr(t) for t in keep)
         cl.stream = _stream_handle(dev)
-        # one entry per cluster (the tracklets are at most the layer-0 clusters;
-        # counting those would wait for the device)
-        cap = max(cl.n, 1)
+        cap = max(cl.n if cl.n <= _COUNT_ABOVE else int((layer == 0).sum()), 1)
         o = {k: torch.empty((cap, *shape), dtype=dtype, device=dev) for k, (dtype, shape) in _FIELDS.items()}
         h = torch.empty(self.nbins, dtype=torch.int32, device=dev) if hist else None
         st = A.tpcca_its_tracks()
@@ -118,6 +122,9 @@ class ItsTracker:
                          vertex=tuple(st.vertex), vfit_sumw=float(st.vfit_sumw))
 
     def track(self, x, y, z, layer, stave, hist: bool = False) -> ItsResult:
+        """One event (device tensors).  The result's tensors are the used parts
+        of arrays of one entry per cluster (per layer-0 cluster in events of
+        more than 2^20 clusters); clone them to keep them without the rest."""
         cl, st, o, h, keep = self._event(x, y, z, layer, stave, hist)
         _check(self.L, self.ctx, self.L.tpcca_its_track(self.ctx, C.byref(cl), C.byref(st)))
         return self._result(st, o, h)
@@ -126,7 +133,8 @@ class ItsTracker:
         """Marshals a batch once (output tensors, structs) and returns
         run(results=True): one tpcca_its_track_batch call on it, for repeated
         calls on the same inputs.  The result tensors of the events are slices
-        of one array per field."""
+        of one array per field (clone those of an event to keep it without the
+        others), overwritten by the next run."""
         events = list(events)
         E = len(events)
         if E == 0:
@@ -138,7 +146,10 @@ class ItsTracker:
         stream = (stream.value or 0) if stream is not None else 0
         keep = [[t.contiguous() for t in e] for e in events]
         cls = np.array([(e[0].shape[0], *(t.data_ptr() for t in e), stream) for e in keep], dtype=_CLUSTERS_DT)
-        cap = np.maximum(cls["n"], 1)
+        cap = cls["n"]
+        if int(cap.sum()) > _COUNT_ABOVE:
+            cap = torch.stack([(e[3] == 0).sum() for e in keep]).cpu().numpy()
+        cap = np.maximum(cap, 1)
         size, at = pieces(cap)
         total = int(size.sum())
         o = {k: torch.empty((total, *shape), dtype=dtype, device=dev) for k, (dtype, shape) in _FIELDS.items()}
@@ -181,7 +192,8 @@ class ItsTracker:
 
     def track_batch(self, events, hist: bool = False) -> list:
         """events: sequence of (x, y, z, layer, stave) device tensors, one
-        tuple per event, all on one device and stream; one library call."""
+        tuple per event, all on one device and stream; one library call.  The
+        results as of prepare_batch."""
         return self.prepare_batch(events, hist)()
 
     def close(self):

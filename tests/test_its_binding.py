@@ -63,3 +63,17 @@ def test_batches_of_any_iterable(devices, form):
 def test_empty_batch():
     t = tracker([])
     assert t.track_batch([]) == [] and t.track_batch(iter([])) == [] and t.L.calls == []
+
+
+def test_large_calls_count_their_layer_0_clusters(monkeypatch):
+    """Up to the limit a call holds an entry per cluster, beyond it one per
+    layer-0 cluster."""
+    monkeypatch.setattr(its, "_COUNT_ABOVE", 60)
+    t = tracker([3, 4])
+    t.track(*event(60))
+    t.track(*event(61))
+    t.track_batch([event(30), event(30)])
+    out = t.track_batch([event(30), event(31)])
+    assert t.L.calls == [[(60, 60)], [(61, 11)], [(30, 30), (30, 30)], [(30, 5), (31, 6)]]
+    assert out[1].tl0.tolist() == [100, 101, 102, 103]
+    assert out[0].in_cov.untyped_storage().nbytes() == 2 * 16 * 15 * 4
