@@ -368,10 +368,11 @@ int tpcca_debug_tracklets(tpcca_ctx* ctx, int64_t cap, int64_t* n_seeds, uint32_
  * FP32 values that any IEEE implementation of the same expressions
  * reproduces).  Evaluates, elementwise on the device with the tracking
  * kernels' compile flags, op 0: the correctly rounded square root used for
- * cosines (argument 0, negative, or >= 2^-96), 1: a[i] / b[i], 2: 1 / a[i],
- * 3: the correctly rounded sqrtf(a[i]) (2 and 3 by the kernels' sequences).  a, b, out are device arrays of n
- * floats (b only for op 1), owned by the caller; work is enqueued on
- * `stream` and finished on return.  TPCCA_E_INVALID for a bad op, size or
+ * cosines (argument 0, negative, or >= 2^-96), 1: a[i] / b[i], 2: 1 / a[i]
+ * (NaN if the kernels' two sequences for it differ), 3: the correctly rounded
+ * sqrtf(a[i]) (2 and 3 by the kernels' short sequences in their ranges).  a,
+ * b, out are device arrays of n floats (b only for op 1), owned by the caller;
+ * work is enqueued on `stream` and finished on return.  TPCCA_E_INVALID for a bad op, size or
  * null pointer, TPCCA_E_DEVICE for a HIP error.  No context needed. */
 int tpcca_debug_fp32(int32_t op, int64_t n, const float* a, const float* b, float* out, void* stream);
 

@@ -59,8 +59,8 @@ __host__ __device__ __forceinline__ float sqrt_rn_normal(float x) {
 // reciprocal (one ulp) and one fused Newton step give the correctly rounded
 // quotient for every float with 2^-125 <= |x| <= 2^125, and NaN for NaN;
 // sqrt(x): g = x rsq(x) and one fused correction give the correctly rounded
-// root for every float in [2^-96, 2^97] (both checked against the library's
-// results over all bit patterns of these ranges).  The host build takes the
+// root for every float in [2^-96, 2^97] (tests/test_gpu_fp32.py compares all
+// of them with the FP64 operation rounded once).  The host build takes the
 // library operations, which round the same.
 __host__ __device__ __forceinline__ float rcp_rn(float x) {   // 2^-125 <= |x| <= 2^125, or NaN
 #if defined(__HIP_DEVICE_COMPILE__)

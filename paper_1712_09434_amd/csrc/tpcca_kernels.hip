@@ -2629,7 +2629,8 @@ namespace {
 // FP32 building blocks of the bit-exact contract, elementwise, compiled with
 // the flags of the tracking kernels: op 0 sqrt_rn_normal(a), 1 a / b,
 // 2 1 / a and 3 sqrt(a), each by the kernels' short sequence in its range
-// and the general one outside.
+// and the general one outside.  Where both reciprocal sequences apply a
+// difference between them gives NaN.
 __global__ __launch_bounds__(TB) void k_fp32_probe(int op, int64_t n, const float* __restrict__ a,
                                                    const float* __restrict__ b, float* __restrict__ out) {
   for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TB) {
@@ -2637,7 +2638,11 @@ __global__ __launch_bounds__(TB) void k_fp32_probe(int op, int64_t n, const floa
     float r;
     if (op == 0) r = sqrt_rn_normal(x);
     else if (op == 1) r = x / b[i];
-    else if (op == 2) r = x == 0.0f || isinf(x) ? rcp_rn_special(x) : rcp_rn_any(x);
+    else if (op == 2) {
+      const float q = rcp_rn_special(x);
+      r = x == 0.0f || isinf(x) ? q : rcp_rn_any(x);
+      if (rcp_key(x) <= kRcpKey && f32_bits(q) != f32_bits(r)) r = __int_as_float(0x7fc00000);
+    }
     else r = x >= 0x1p-96f && x <= 0x1p+97f ? sqrt_rn_pos(x) : sqrtf(x);
     out[i] = r;
   }

@@ -115,3 +115,41 @@ def test_sqrtf():
     sub = (rng.integers(1, 1 << 23, 1 << 16, dtype=np.uint32)).view(np.float32)   # subnormals
     a = np.concatenate([a, sub, np.array([0.0, -0.0], np.float32)])
     same_bits(device_op(3, a), np.sqrt(a), "sqrtf")
+
+
+@pytest.mark.parametrize("op,lo,hi,signs", [(2, -125, 125, (1, -1)), (3, -96, 97, (1,))])
+def test_short_sequences_over_all_bit_patterns(op, lo, hi, signs):
+    """The short sequences of 1 / x (both of them: the tap gives NaN where they
+    differ) and sqrt(x) on every float of the ranges they are stated for,
+    against the FP64 operation rounded to FP32.  That rounding is innocent: 53
+    bits are more than twice 24 and two, and the results are normal."""
+    from paper_1712_09434_amd import _abi
+    L = _abi.load()
+    first, last = (int(np.float32(2.0 ** k).view(np.uint32)) for k in (lo, hi))
+    st = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    step = 1 << 26
+    out = torch.empty(step, dtype=torch.float32, device="cuda:0")
+    for sign in signs:
+        print(f"[gpu] op {op}: {last + 1 - first} floats of sign {sign}", flush=True)
+        for b in range(first, last + 1, step):
+            n = min(step, last + 1 - b)
+            a = sign * torch.arange(b, b + n, dtype=torch.int32, device="cuda:0").view(torch.float32)
+            assert L.tpcca_debug_fp32(op, n, C.c_void_p(a.data_ptr()), None, C.c_void_p(out.data_ptr()), st) == 0
+            want = (a.double().reciprocal() if op == 2 else a.double().sqrt()).float()
+            bad = torch.nonzero(out[:n].view(torch.int32) != want.view(torch.int32))
+            assert bad.numel() == 0, (hex(b), bad.numel(), a[bad[:4, 0]], out[bad[:4, 0]], want[bad[:4, 0]])
+
+
+def test_short_sequences_at_the_ends_of_their_ranges():
+    """Around the ranges' ends, where the kernels change to the general forms,
+    and zeros, infinities, NaN and subnormals."""
+    inf = np.float32(np.inf)
+    x = [np.float32(2.0 ** k) for k in (-149, -127, -126, -125, -124, 124, 125, 126, 127)]
+    x += [np.nextafter(v, to) for v in x for to in (np.float32(0), inf)] + [np.float32(v) for v in (0, inf, np.nan)]
+    x = np.array(x + [-v for v in x], np.float32)
+    with np.errstate(all="ignore"):
+        same_bits(device_op(2, x), np.float32(1.0) / x, "reciprocal at the ends")
+        x = [np.float32(2.0 ** k) for k in (-149, -126, -97, -96, -95, 96, 97, 98, 127)]
+        x += [np.nextafter(v, to) for v in x for to in (np.float32(0), inf)]
+        x = np.array(x + [np.float32(v) for v in (0, -0.0, -1, inf, -inf, np.nan)], np.float32)
+        same_bits(device_op(3, x), np.sqrt(x), "square root at the ends")
