@@ -39,7 +39,7 @@ struct CalWs {
   float* hy;
   float* hz;
   float* gx;               // [H] dx-derivative of the step ending at the hit
-  float* gy;               // (not used: the correction leaves y as it is)
+  float* gy;               // not used, null on the device (the correction leaves y as it is)
   float* gz;
   float* gpt;              // [H] x-adjoint point terms (seed chord, vertex hop), at a track's first, third and last hit
   float4* bva;             // [H] the four non-zero x-direction B-splines at the hit

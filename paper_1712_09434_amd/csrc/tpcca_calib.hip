@@ -1085,7 +1085,7 @@ __global__ void k_cal_zero(CalWs c) {
 hipError_t run_calib(const CalWs& c, hipStream_t st) {
   // every array the kernels touch must be set before anything is launched
   const void* need[] = {c.hit_off, c.hit_id, c.k_prior, c.cx, c.cy, c.cz, c.csec, c.dl, c.tau, c.map,
-                        c.hx, c.hy, c.hz, c.gx, c.gy, c.gz, c.gpt, c.bva, c.bvb, c.bsp, c.dzt,
+                        c.hx, c.hy, c.hz, c.gx, c.gz, c.gpt, c.bva, c.bvb, c.bsp, c.dzt,
                         c.part, c.tflag, c.tndf, c.ckpt,
                         c.seg, c.chunk, c.out, c.ndf_sum, c.err};
   for (const void* p : need)

@@ -731,7 +731,7 @@ namespace {
 // pad rows and checkpoint stride K; host inputs get staged copies.
 struct GradLayout {
   int K = 0, nck = 0, nseg = 0;
-  size_t o_hx = 0, o_hy = 0, o_hz = 0, o_gx = 0, o_gy = 0, o_gz = 0, o_gpt = 0;
+  size_t o_hx = 0, o_hy = 0, o_hz = 0, o_gx = 0, o_gz = 0, o_gpt = 0;
   size_t o_bva = 0, o_bvb = 0, o_bsp = 0, o_dzt = 0;
   size_t o_part = 0, o_tf = 0, o_tn = 0, o_ck = 0, o_sg = 0, o_chunk = 0, o_out = 0, o_ndf = 0, o_err = 0;
   size_t o_off = 0, o_ids = 0, o_kp = 0, o_ext = 0, o_uv = 0;
@@ -758,7 +758,7 @@ GradLayout grad_layout(int64_t T, int64_t H, int64_t NC, int S, int R, int K, bo
   const int64_t nchunk = (T + kChunk - 1) / kChunk;
   Layout L;
   g.o_hx = L.take<float>(H); g.o_hy = L.take<float>(H); g.o_hz = L.take<float>(H);
-  g.o_gx = L.take<float>(H); g.o_gy = L.take<float>(H); g.o_gz = L.take<float>(H); g.o_gpt = L.take<float>(H);
+  g.o_gx = L.take<float>(H); g.o_gz = L.take<float>(H); g.o_gpt = L.take<float>(H);
   g.o_bva = L.take<float4>(H); g.o_bvb = L.take<float4>(H); g.o_bsp = L.take<int32_t>(H);
   g.o_dzt = L.take<float>(H);
   g.o_part = L.take<float>(T * kPart);
@@ -852,7 +852,7 @@ hipError_t grad_bind(const tpcca_ctx* c, CalWs& w, char* b, const GradLayout& gl
   }
   w.cpack = gl.o_pack ? (float4*)(b + gl.o_pack) : nullptr;
   w.hx = (float*)(b + gl.o_hx); w.hy = (float*)(b + gl.o_hy); w.hz = (float*)(b + gl.o_hz);
-  w.gx = (float*)(b + gl.o_gx); w.gy = (float*)(b + gl.o_gy); w.gz = (float*)(b + gl.o_gz);
+  w.gx = (float*)(b + gl.o_gx); w.gz = (float*)(b + gl.o_gz);
   w.gpt = (float*)(b + gl.o_gpt);
   w.bva = (float4*)(b + gl.o_bva); w.bvb = (float4*)(b + gl.o_bvb); w.bsp = (int32_t*)(b + gl.o_bsp);
   w.dzt = (float*)(b + gl.o_dzt);
