@@ -1006,14 +1006,20 @@ int tpcca_refit_grad(tpcca_ctx* c, const tpcca_tracks* t, const tpcca_calib* cal
   }
   const int64_t H = H32;
   if (H < 0) return fail(c, TPCCA_E_INVALID, "negative hit count");
-  const GradLayout gl = grad_layout(T, H, NC, S, c->R, c->tune.ckpt_every, t->mem == TPCCA_MEM_HOST,
-                                    k.mem == TPCCA_MEM_HOST, cal->mem == TPCCA_MEM_HOST,
-                                    g->mem == TPCCA_MEM_HOST && g->track_flag, grad_packs(H, NC));
-  if (gl.bytes > c->gscratch_bytes) {
+  GradLayout gl;
+  for (int pack = grad_packs(H, NC) ? 1 : 0;; --pack) {
+    gl = grad_layout(T, H, NC, S, c->R, c->tune.ckpt_every, t->mem == TPCCA_MEM_HOST, k.mem == TPCCA_MEM_HOST,
+                     cal->mem == TPCCA_MEM_HOST, g->mem == TPCCA_MEM_HOST && g->track_flag, pack != 0);
+    if (gl.bytes <= c->gscratch_bytes) break;
     if (c->gscratch) { (void)hipFree(c->gscratch); c->gscratch = nullptr; c->gscratch_bytes = 0; }
-    he = hipMalloc((void**)&c->gscratch, gl.bytes + gl.bytes / 4);
-    if (he != hipSuccess) { c->gscratch = nullptr; (void)hipGetLastError(); return fail(c, TPCCA_E_NOMEM, "gradient scratch allocation failed"); }
-    c->gscratch_bytes = gl.bytes + gl.bytes / 4;
+    if (hipMalloc((void**)&c->gscratch, gl.bytes + gl.bytes / 4) == hipSuccess) {
+      c->gscratch_bytes = gl.bytes + gl.bytes / 4;
+      break;
+    }
+    c->gscratch = nullptr;
+    (void)hipGetLastError();
+    // (without memory for the packed clusters the hits read the arrays)
+    if (!pack) return fail(c, TPCCA_E_NOMEM, "gradient scratch allocation failed");
   }
   CalWs w{};
   he = grad_bind(c, w, c->gscratch, gl, t, cal, g, H, st);
