@@ -261,7 +261,8 @@ int tpcca_track_batch(tpcca_ctx* ctx, int32_t n_events, const tpcca_clusters* ev
  * n_tracks / n_hits hold the merged counts.  seg_link (optional, device,
  * [segments->n_tracks]) receives each segment's outer partner or -1.
  * TPCCA_E_INVALID for host memory, null arrays, a segment with fewer than
- * 3 hits, a bad sector or hit id. */
+ * 3 hits, a bad sector or hit id (of a segment's first or last hit, or of any
+ * hit of a chain that is refitted). */
 int tpcca_merge(tpcca_ctx* ctx, const tpcca_tracks* segments, tpcca_tracks* merged, int32_t* seg_link);
 
 /* Time-frame tracking (Sec. "Track reconstruction in the TPC": with
@@ -342,9 +343,9 @@ int tpcca_refit_grad(tpcca_ctx* ctx, const tpcca_tracks* tracks, const tpcca_cal
  *   - the checkpoint stride is the largest one up to the tuned ckpt_every
  *     whose workspace fits the scratch (results do not depend on it); if
  *     none fits, TPCCA_E_LIMIT and nothing runs.  Per track the workspace
- *     is 68 bytes per hit plus 5.5 KB (stride 9-12) to 28 KB (stride 160)
- *     of kept states: for tracks of 130 hits the scratch holds about 3,600
- *     of them at stride 160 and about 9,300 at the most compact stride;
+ *     is 64 bytes per hit plus 5.5 KB (stride 9-12) to 28 KB (stride 160)
+ *     of kept states: for tracks of 130 hits the scratch holds about 3,650
+ *     of them at stride 160 and about 9,650 at the most compact stride;
  *   - every call on a GPU, from any context, uses that GPU's one array:
  *     calls that overlap in time on one GPU (two streams, two threads)
  *     race and give wrong results.  The array keeps the last call's
@@ -372,8 +373,9 @@ int tpcca_debug_tracklets(tpcca_ctx* ctx, int64_t cap, int64_t* n_seeds, uint32_
  * (NaN if the kernels' two sequences for it differ), 3: the correctly rounded
  * sqrtf(a[i]) (2 and 3 by the kernels' short sequences in their ranges).  a,
  * b, out are device arrays of n floats (b only for op 1), owned by the caller;
- * work is enqueued on `stream` and finished on return.  TPCCA_E_INVALID for a bad op, size or
- * null pointer, TPCCA_E_DEVICE for a HIP error.  No context needed. */
+ * work is enqueued on `stream` and finished on return.  TPCCA_E_INVALID for a
+ * bad op, size or null pointer, TPCCA_E_DEVICE for a HIP error.  No context
+ * needed. */
 int tpcca_debug_fp32(int32_t op, int64_t n, const float* a, const float* b, float* out, void* stream);
 
 /* Replace / read the launch tuning of a context (results never change). */

@@ -724,8 +724,8 @@ __global__ __launch_bounds__(64) void k_its_follow(ItsWs w) {
 // barrier each, exchanges between lanes without LDS inside a row (a wave
 // butterfly through LDS, the waves' sums and the solution by thread 0 with
 // four barriers took 38 us for one event of 60 tracks and 78 for 20 of 3,000,
-// this way 18 and 41; six tracks a thread in registers: with four 16 and 55,
-// with eight, which spill, 22 and 73).
+// this way 18 and 41; six tracks a thread kept: with four 16 and 55,
+// with eight, which spill 108 registers instead of 40, 22 and 73).
 constexpr int TBV = 512;
 constexpr int kVReg = 6;
 constexpr int kVRows = TBV / 16;   // rows of 16 lanes

@@ -1265,7 +1265,7 @@ __device__ __forceinline__ void wave_pairs(const Ws& w, bool has, float xi, floa
 // its neighbours alone is left to k_links.  Results do not depend on the
 // order.  Bound by its instructions: a wave or workgroup per row left half
 // the lanes idle on rows of 33 clusters and staged every row twice (64 small
-// events 583 us, this way 319; 0.77 M clusters 44 and 37).
+// events 583 us, this way 315; 0.77 M clusters 44 and 38).
 constexpr int kLinkRows = 8;             // rows of a band, at most
 // Entries staged, at most and at least (five and six workgroups share a
 // compute unit's LDS).
