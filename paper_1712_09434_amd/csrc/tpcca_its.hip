@@ -56,6 +56,10 @@ constexpr int kLayers = 6;
 constexpr int kStaves = 64;      // per layer, at most
 constexpr int kBins = 4096;      // vertexer histogram bins, at most
 constexpr int kPerEv = kLayers * kStaves;   // stave slots per event
+// Words between the events' pair counters: every workgroup of the pair
+// histogram adds to its event's, and with eight of them in a cache line the
+// histogram of 20 central events takes 40 us instead of 34.
+constexpr int kPairStride = 4;
 
 // Geometry tables in device memory (FP32 values of FP64 expressions):
 // stave centre cos/sin and wedge boundary cos/sin per layer.
@@ -104,7 +108,7 @@ struct ItsWs {
   uint32_t* l0list;        // [n] layer-0 clusters in id order
   uint32_t* hist;          // [E * nbins]
   unsigned long long* zsum;   // [E * nbins] fixed-point sums of the pairs' z per bin
-  unsigned long long* vsum;   // [E] pairs
+  unsigned long long* vsum;   // [E * kPairStride] pairs
   float* vzd;              // [E * 2]: vertex z, found flag
   int32_t* vpeak;          // [E]
   unsigned long long* best0;  // [n] (score bits << 32) | layer-1 id
@@ -135,7 +139,7 @@ __global__ __launch_bounds__(TB) void k_its_init(ItsWs w) {
   const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
   if (i < (int64_t)w.E * kPerEv + 1) w.scnt[i] = 0u;
   if (i < (int64_t)w.E * w.nbins) { w.hist[i] = 0u; w.zsum[i] = 0ull; }
-  if (i < w.E) w.vsum[i] = 0ull;
+  if (i < (int64_t)w.E * kPairStride) w.vsum[i] = 0ull;
   if (i < w.n) w.best1[i] = ~0ull;
   if (i == 0) w.err[0] = 0u;
 }
@@ -364,7 +368,7 @@ __global__ __launch_bounds__(TB) void k_its_vpairs(ItsWs w) {
     // the pair count of the workgroup's first event is summed in LDS first
     if (gl == 0 && cnt) {
       if (c.e == e0) atomicAdd(&s_n, cnt);
-      else atomicAdd(&w.vsum[c.e], cnt);
+      else atomicAdd(&w.vsum[c.e * kPairStride], cnt);
     }
   }
   __syncthreads();
@@ -373,7 +377,7 @@ __global__ __launch_bounds__(TB) void k_its_vpairs(ItsWs w) {
       atomicAdd(&w.hist[(int64_t)e0 * w.nbins + bb], h[bb]);
       atomicAdd(&w.zsum[(int64_t)e0 * w.nbins + bb], s_z[bb]);
     }
-  if (threadIdx.x == 0 && s_n) atomicAdd(&w.vsum[e0], s_n);
+  if (threadIdx.x == 0 && s_n) atomicAdd(&w.vsum[e0 * kPairStride], s_n);
 }
 
 // fullest bin of each event (ties: lower) and the mean z of the pairs in it
@@ -1033,7 +1037,7 @@ int tpcca_its_track_batch(tpcca_its_ctx* c, int32_t E, const tpcca_its_clusters*
   // the event and output tables back to back (one upload), the per-event
   // results back to back (one download)
   const size_t up_ev = sizeof(ItsEvIn) * (E + 1), up_bytes = up_ev + sizeof(tpcca_its_tracks) * E;
-  const size_t r_vsum = 0, r_vres = r_vsum + 8 * (size_t)E, r_vzd = r_vres + 8 * 8 * (size_t)E;
+  const size_t r_vsum = 0, r_vres = r_vsum + 8 * kPairStride * (size_t)E, r_vzd = r_vres + 8 * 8 * (size_t)E;
   const size_t r_pk = r_vzd + 8 * (size_t)E, r_toff = r_pk + 4 * (size_t)E, r_err = r_toff + 4 * ((size_t)E + 1);
   const size_t res_bytes = r_err + 8;
   const size_t o_up = take(up_bytes), o_res = take(res_bytes);
@@ -1138,7 +1142,7 @@ int tpcca_its_track_batch(tpcca_its_ctx* c, int32_t E, const tpcca_its_clusters*
     tpcca_its_tracks& o = outs[e];
     o.n_tracklets = (int64_t)(toff[e + 1] - toff[e]);
     fits = fits && o.n_tracklets <= o.cap;
-    o.n_pairs = (int64_t)vs[e];
+    o.n_pairs = (int64_t)vs[kPairStride * e];
     o.peak = pk[e];
     o.vz = vz[2 * e];
     o.vz_ok = vz[2 * e + 1] != 0.0f ? 1 : 0;
