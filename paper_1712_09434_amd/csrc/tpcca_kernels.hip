@@ -1793,7 +1793,7 @@ __device__ __forceinline__ bool accepted(float X, const Acc& a, const float p[5]
 // step's plane, grid and chain record are loaded before the update, which
 // covers their latency; phase changes are settled in one place; quotients
 // and roots take the short sequences.  On one sector's 17 k clusters the
-// kernel takes 285 us (476 with one lane per seed, a test per loaded entry
+// kernel takes 277 us (476 with one lane per seed, a test per loaded entry
 // and no L2 warming), on 0.77 M clusters 345 (494), on 3.8 M, where three
 // waves per SIMD share the issue slots, 708 (805).
 // With several lanes per seed, groups that have finished wait until a quarter
